@@ -295,9 +295,9 @@ int axipcg_laguerre_coeffs_alpha(int n, int alpha, double eta, int nt, double t_
                                  const double *f_host, double *g_host, void *stream);
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the same as
- * axipcg_laguerre_coeffs_alpha and the same kernel, with the staged samples
- * and coefficients in a fixed device array of the library (1 MiB per device,
- * held until the process ends) instead of per-call hipMalloc'd buffers.  It
+ * axipcg_laguerre_coeffs_alpha and the same kernel, with the staged samples,
+ * coefficients and partial sums in a fixed device array of the library (5 MiB
+ * per device, held until the process ends) instead of per-call hipMalloc'd buffers.  It
  * calls no hipMalloc, hipFree or other allocating routine.  Limit:
  * nt + n <= 131072, else AXIPCG_EINVAL.  Synchronises `stream` before
  * returning.  Every call on one device shares that array: calls that overlap
