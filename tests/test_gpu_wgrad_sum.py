@@ -1,0 +1,35 @@
+"""Weight gradients of the learned guess where the sum over the workgroups'
+partials (one per 64-pixel segment) changes form: fewer partials than one
+unrolled round of 128, exactly one, and a round with a remainder.
+
+Tolerance: data gradients and activations are rounded to BF16 (2^-8) at each of
+six layers, so a layer's gradient is good to 2e-2 of its norm."""
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("segments", [2, 7, 121, 128, 129, 263])
+def test_weight_gradient_over_segments(orc, segments):
+    from oracle import nn as onn
+    from paper_1002_3094_amd import axipcg as ax
+    nr, nz = segments, 64
+    ex = synth.nn_example(nr, nz, seed=segments)
+    q = np.full((nr, nz), 0.5)
+    params = onn.init_params(5, last_zero=False)
+    params[onn.OFFSETS[5]:onn.OFFSETS[5] + 9 * 32] *= 0.001
+    oop = orc.operator_from_cells(ex["kappa"], q)
+    with ax.op_create(ex["kappa"], q) as op, ax.nn_create(nr, nz, params) as net:
+        u1, u2 = dev(ex["u1"]), dev(ex["u2"])
+        ax.nn_forward(net, u1, u2, dev(ex["b"]), dev(ex["kappa"]), dev(np.zeros((nr, nz))))
+        ax.nn_backward(op, net, u1, u2, dev(ex["ut"]))
+        _, grad = ax.nn_get_params(net)
+    _, cache = onn.forward(params, ex["u1"], ex["u2"], ex["b"], ex["kappa"])
+    _, ref = onn.backward(params, cache, lambda e: orc.apply(oop, e), ex["ut"])
+    ends = list(onn.OFFSETS) + [len(params)]
+    for lo, hi in zip(ends[:6], ends[1:7]):
+        assert np.linalg.norm(grad[lo:hi] - ref[lo:hi]) <= 2e-2 * np.linalg.norm(ref[lo:hi])
