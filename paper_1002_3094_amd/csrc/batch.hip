@@ -47,9 +47,10 @@ struct BatchSetup {
     ~BatchSetup() { if (hs) (void)hipHostFree(hs); }
 };
 
-// tau, rho2: the Chebyshev parameters of each member (NULL for PCG).
+// tau, rho2: the Chebyshev parameters of each member (NULL for PCG); chunk:
+// columns per SpMV tile.
 void batch_setup(BatchSetup &B, int n, Operator *const *ops, const double *const *b, double *const *x, int prec,
-                 const double *tau, const double *rho2, hipStream_t s)
+                 const double *tau, const double *rho2, int chunk, hipStream_t s)
 {
     B.h.resize(n);
     std::vector<int> plan(n);
@@ -62,7 +63,7 @@ void batch_setup(BatchSetup &B, int n, Operator *const *ops, const double *const
         d.row_start = B.rows;
         d.tri_start = B.tri;
         d.sp_start = B.spt;
-        d.n_sp = batch_spmv_tiles(op.nr, op.nz);
+        d.n_sp = batch_spmv_tiles(op.nr, op.nz, chunk);
         B.spt += d.n_sp;
         size_t shm = 0;
         batch_tri_geom(op.nr, prec, BatchSetup::M, &d.tri_S, &d.tri_L, &d.tri_Lp, &d.tri_pitch, &shm);
@@ -180,10 +181,10 @@ int batch_finish(const BatchSetup &B, int n, Operator *const *ops, const double 
 void batch_start(const BatchSetup &B, int n, int prec, const TriGate &g, int zinv_mode, hipStream_t s)
 {
     launch_b_init(B.d, n, B.rows, s);
-    for (const BatchPlan &pl : B.plans) launch_b_zfwd(B.dp, pl, prec, BZ_START, 0, s);
+    for (const BatchPlan &pl : B.plans) launch_b_zfwd(B.dp, pl, prec, BZ_START, s);
     launch_b_tridiag(B.d, n, B.tri, prec, g, BatchSetup::M, B.tri_shm, s);
     launch_b_zero(B.d, n, B.rows, s);
-    for (const BatchPlan &pl : B.plans) launch_b_zinv(B.dp, pl, prec, zinv_mode, false, s);
+    for (const BatchPlan &pl : B.plans) launch_b_zinv(B.dp, pl, prec, zinv_mode, false, 0, s);
 }
 
 int batch_impl(int n, Operator *const *ops, const double *const *b, double *const *x, double rtol, int maxit,
@@ -192,7 +193,7 @@ int batch_impl(int n, Operator *const *ops, const double *const *b, double *cons
     const bool single = (flags & AXIPCG_FLAG_SINGLE_LAUNCH) != 0;
     const bool pr = (flags & AXIPCG_FLAG_POLAK_RIBIERE) != 0;
     BatchSetup B;
-    batch_setup(B, n, ops, b, x, prec, nullptr, nullptr, s);
+    batch_setup(B, n, ops, b, x, prec, nullptr, nullptr, single ? BATCH_ONE_CHUNK : SPMV_CHUNK, s);
     TriGate g;
     g.mode = 2;
     g.rtol2 = rtol * rtol;
@@ -240,10 +241,10 @@ int batch_impl(int n, Operator *const *ops, const double *const *b, double *cons
         batch_start(B, n, prec, g, 2, s);
         batch_iterate(B, n, maxit, s, [&](int it) {
             const int parity = it & 1;
-            launch_b_spmv(B.d, n, B.spt, pr, parity, s);
-            for (const BatchPlan &pl : B.plans) launch_b_zfwd(B.dp, pl, prec, BZ_PCG, parity, s);
+            launch_b_spmv(B.d, n, B.spt, prec, pr, parity, s);
+            for (const BatchPlan &pl : B.plans) launch_b_zfwd(B.dp, pl, prec, BZ_PCG, s);
             launch_b_tridiag(B.d, n, B.tri, prec, gi, BatchSetup::M, B.tri_shm, s);
-            for (const BatchPlan &pl : B.plans) launch_b_zinv(B.dp, pl, prec, 1, pr, s);
+            for (const BatchPlan &pl : B.plans) launch_b_zinv(B.dp, pl, prec, 1, pr, it, s);
         });
     }
     return batch_finish(B, n, ops, b, x, (flags & AXIPCG_FLAG_TRUE_RESIDUAL) != 0, st, s);
@@ -264,7 +265,7 @@ int batch_cheb_impl(int n, Operator *const *ops, const double *const *b, double 
         rho2[p] = ((1.0 - xi) / (1.0 + xi)) * ((1.0 - xi) / (1.0 + xi));
     }
     BatchSetup B;
-    batch_setup(B, n, ops, b, x, prec, tau.data(), rho2.data(), s);
+    batch_setup(B, n, ops, b, x, prec, tau.data(), rho2.data(), SPMV_CHUNK, s);
     TriGate g;
     g.mode = 2;
     g.rtol2 = rtol * rtol;
@@ -275,9 +276,9 @@ int batch_cheb_impl(int n, Operator *const *ops, const double *const *b, double 
     gi.rr_rows = 1;
     batch_iterate(B, n, maxit, s, [&](int) {
         launch_b_cheb(B.d, n, B.rows, s);
-        for (const BatchPlan &pl : B.plans) launch_b_zfwd(B.dp, pl, prec, BZ_CHEB, 0, s);
+        for (const BatchPlan &pl : B.plans) launch_b_zfwd(B.dp, pl, prec, BZ_CHEB, s);
         launch_b_tridiag(B.d, n, B.tri, prec, gi, BatchSetup::M, B.tri_shm, s);
-        for (const BatchPlan &pl : B.plans) launch_b_zinv(B.dp, pl, prec, 3, false, s);
+        for (const BatchPlan &pl : B.plans) launch_b_zinv(B.dp, pl, prec, 3, false, 0, s);
     });
     return batch_finish(B, n, ops, b, x, true_residual, st, s);
 }

@@ -8,10 +8,11 @@
 //              forward z-transform of r              items: transform blocks
 //              start test; r-solves                  items: mode groups
 //              x = 0 where b = 0; inverse, r.z       items: rows; transform blocks
-//   iteration  SpMV: beta, p update, q = A p, p.q   items: SpMV tiles
-//              alpha; x, r update; forward           items: transform blocks
+//   iteration  SpMV: beta, x, p update, q = A p, p.q items: SpMV tiles
+//              alpha; r update; forward              items: transform blocks
 //              stop test; r-solves                   items: mode groups
-//              inverse transform, r.z                items: transform blocks
+//              inverse transform, r.z (or the last x update of a problem
+//              that stopped)                         items: transform blocks
 // A phase deals its items to the workgroups round-robin.  An item is one
 // workgroup of the multi-launch form (spmv.h, xform.h), so every problem
 // goes through the operations of the multi-launch batch in the same order
@@ -46,26 +47,26 @@ struct SingleArgs {
 // PH 0: start forward (plain), 1: step forward (fused), 2: start inverse,
 // 3: step inverse.
 template <typename T, int PH, int R2>
-__device__ __forceinline__ void wave_item(const ProbDesc *d, int n, int g, int parity, bool pr)
+__device__ __forceinline__ void wave_item(const ProbDesc *d, int n, int g, int it, bool pr)
 {
     static_assert(wave_rows<T, R2>() == 4, "one row per wave of a 256-thread workgroup");
-    if constexpr (PH == 0) b_zfwd_w_item<T, false, R2, true>(d, n, g, parity);
-    else if constexpr (PH == 1) b_zfwd_w_item<T, true, R2, true>(d, n, g, parity);
-    else if constexpr (PH == 2) b_zinv_w_item<T, 2, R2>(d, n, g, false);
-    else b_zinv_w_item<T, 1, R2>(d, n, g, pr);
+    if constexpr (PH == 0) b_zfwd_w_item<T, false, R2, true>(d, n, g);
+    else if constexpr (PH == 1) b_zfwd_w_item<T, true, R2, true>(d, n, g);
+    else if constexpr (PH == 2) b_zinv_w_item<T, 2, R2>(d, n, g, false, 0);
+    else b_zinv_w_item<T, 1, R2>(d, n, g, pr, it);
 }
 
 template <typename T, int PH, bool TWLDS>
-__device__ __forceinline__ void block_item(const ProbDesc *d, int n, int g, int parity, bool pr)
+__device__ __forceinline__ void block_item(const ProbDesc *d, int n, int g, int it, bool pr)
 {
-    if constexpr (PH == 0) b_zfwd_item<T, false, TWLDS, true>(d, n, g, parity);
-    else if constexpr (PH == 1) b_zfwd_item<T, true, TWLDS, true>(d, n, g, parity);
-    else if constexpr (PH == 2) b_zinv_item<T, 2, TWLDS>(d, n, g, false);
-    else b_zinv_item<T, 1, TWLDS>(d, n, g, pr);
+    if constexpr (PH == 0) b_zfwd_item<T, false, TWLDS, true>(d, n, g);
+    else if constexpr (PH == 1) b_zfwd_item<T, true, TWLDS, true>(d, n, g);
+    else if constexpr (PH == 2) b_zinv_item<T, 2, TWLDS>(d, n, g, false, 0);
+    else b_zinv_item<T, 1, TWLDS>(d, n, g, pr, it);
 }
 
 template <typename T, int RMAX, int PH>
-__device__ __forceinline__ void tr_phase(const SingleArgs &A, int parity, bool pr)
+__device__ __forceinline__ void tr_phase(const SingleArgs &A, int it, bool pr)
 {
     const int total = A.base[A.nplan];
     for (int t = blockIdx.x; t < total; t += gridDim.x) {
@@ -74,17 +75,17 @@ __device__ __forceinline__ void tr_phase(const SingleArgs &A, int parity, bool p
         const ProbDesc *d = A.dp + A.off[pl];
         const int n = A.np[pl], g = t - A.base[pl];
         switch (A.r2[pl]) {
-        case 2: wave_item<T, PH, 2>(d, n, g, parity, pr); break;
-        case 4: wave_item<T, PH, 4>(d, n, g, parity, pr); break;
+        case 2: wave_item<T, PH, 2>(d, n, g, it, pr); break;
+        case 4: wave_item<T, PH, 4>(d, n, g, it, pr); break;
         case 8:
-            if constexpr (RMAX >= 8) wave_item<T, PH, 8>(d, n, g, parity, pr);
+            if constexpr (RMAX >= 8) wave_item<T, PH, 8>(d, n, g, it, pr);
             break;
         case 16:
-            if constexpr (RMAX >= 16) wave_item<T, PH, 16>(d, n, g, parity, pr);
+            if constexpr (RMAX >= 16) wave_item<T, PH, 16>(d, n, g, it, pr);
             break;
         default:
-            if (A.twl[pl]) block_item<T, PH, true>(d, n, g, parity, pr);
-            else block_item<T, PH, false>(d, n, g, parity, pr);
+            if (A.twl[pl]) block_item<T, PH, true>(d, n, g, it, pr);
+            else block_item<T, PH, false>(d, n, g, it, pr);
         }
         __syncthreads();   // the item's LDS is free for the next one
     }
@@ -133,16 +134,15 @@ __device__ __forceinline__ bool single_run(const SingleArgs &A, int *flag)
     int parity = 0;
     for (int it = 0; it < A.maxit && any_running(A); ++it) {
         for (int g = blockIdx.x; g < A.spt; g += G) {
-            b_spmv_item<PR>(A.d, A.n, g, parity);
+            b_spmv_item<T, PR, BATCH_ONE_CHUNK>(A.d, A.n, g, parity);
             __syncthreads();
         }
         if (!sync()) return false;
-        tr_phase<T, RMAX, 1>(A, parity, PR);
+        tr_phase<T, RMAX, 1>(A, it, PR);
         if (!sync()) return false;
         tri_phase<T>(A, A.g_step);
         if (!sync()) return false;
-        if (!any_running(A)) break;
-        tr_phase<T, RMAX, 3>(A, parity, PR);
+        tr_phase<T, RMAX, 3>(A, it, PR);
         if (!sync()) return false;
         parity ^= 1;
     }

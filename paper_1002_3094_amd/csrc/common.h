@@ -53,10 +53,13 @@ struct PcgState {
     double pad[3];
     int done;        // 0 running, 1 converged, 2 breakdown, 3 maxit, 4 b = 0
     int iters;       // completed iterations (r-solve kernel)
-    int cur;         // iteration being processed (forward kernel)
     int maxit;
     int flags;
-    int pad2[3];
+    struct Step {    // of the forward kernel, written as one piece
+        double alpha;   // step length of iteration `cur` (0 at the start)
+        int cur;        // iteration being processed
+        int pad;
+    } step;
 };
 
 // Progress of a solve as the host sees it, in coherent pinned host memory:
@@ -165,7 +168,7 @@ struct Operator {
 // of a row-indexed launch belongs to the problem whose [row_start, row_start +
 // nr) range holds g; of the r-solve launch, [tri_start, tri_start + nz / M);
 // of its transform launch, [tr_start, tr_start + n_tr); of the SpMV launch
-// (one tile of BATCH_SPMV_RW rows by SPMV_CHUNK columns per workgroup),
+// (one tile of BATCH_SPMV_RW rows by a chunk of columns per workgroup),
 // [sp_start, sp_start + n_sp).
 struct ProbDesc {
     int nr, nz, bc_z;
@@ -265,32 +268,43 @@ __device__ inline double block_sum(double v, double *sm)
 // reads of one round are in flight together rather than one latency apiece.
 // total_issue and total_finish split the same sum in two: the first
 // round's loads issued early, the additions (in the same order) later.
+// (NV loads per thread in it; a reader that has few partials to sum takes
+// fewer registers with a smaller NV).
+template <int NV = 8>
 struct TotalLoads {
-    double v[8];
+    double v[NV];
 };
 
-__device__ inline void total_issue(const double *__restrict__ parts, int n, TotalLoads &t)
+template <int NV>
+__device__ inline void total_issue(const double *__restrict__ parts, int n, TotalLoads<NV> &t)
 {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < NV; ++j) {
         const int i = (int)threadIdx.x + j * (int)blockDim.x;
         t.v[j] = (i < n) ? parts[i] : 0.0;
     }
 }
 
-__device__ inline double total_finish(const double *__restrict__ parts, int n, const TotalLoads &t, double *sm)
+template <int NV>
+__device__ inline double total_finish(const double *__restrict__ parts, int n, const TotalLoads<NV> &t, double *sm)
 {
     const int nt = blockDim.x;
-    double s = 0.0;
-    s += ((t.v[0] + t.v[1]) + (t.v[2] + t.v[3])) + ((t.v[4] + t.v[5]) + (t.v[6] + t.v[7]));
-    for (int base = 8 * nt; base < n; base += 8 * nt) {
-        double v[8];
+    auto tree = [](const double *v) {
+        double a = 0.0;
+        if constexpr (NV == 8) a += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        else a += v[0] + v[1];
+        return a;
+    };
+    static_assert(NV == 8 || NV == 2, "eight or two loads per round");
+    double s = tree(t.v);
+    for (int base = NV * nt; base < n; base += NV * nt) {
+        double v[NV];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NV; ++j) {
             const int i = base + (int)threadIdx.x + j * nt;
             v[j] = (i < n) ? parts[i] : 0.0;
         }
-        s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        s += tree(v);
     }
     s = block_sum(s, sm);
     const int nw = (blockDim.x + 63) >> 6;

@@ -8,12 +8,12 @@ namespace axipcg {
 // Forward z-transform of every r-row (§4.2 eq. (38)).
 //  plain: spec = S rin (with `state` set: skipped once the stop test has fired)
 //  fused PCG step (after the SpMV kernel): alpha = rho / p.q from the SpMV
-//    partials (p.q <= 0 marks a breakdown), x += alpha p, r -= alpha q,
-//    one ||r||^2 partial per workgroup, then spec = S r.
+//    partials (p.q <= 0 marks a breakdown), r -= alpha q, one ||r||^2
+//    partial per workgroup, then spec = S r.
 struct ZfwdArgs {
     const double *rin = nullptr;           // plain mode input
-    double *x = nullptr, *r = nullptr;     // fused mode
-    const double *p = nullptr, *q = nullptr;
+    double *r = nullptr;                   // fused mode
+    const double *q = nullptr;
     PcgState *state = nullptr;             // fused: gate + scalars
     int n_pq = 0;                          // fused: number of p.q partials
     bool fused = false;
@@ -44,7 +44,8 @@ struct TriGate {
 };
 void launch_tridiag(const Operator &op, int prec, const TriGate &g, hipStream_t s);
 
-// Inverse z-transform of every row: zout = S^T spec.
+// Inverse z-transform of every row: zout = S^T spec (double in mode 0; in the
+// preconditioner's own type in the PCG modes, whose SpMV reads it so).
 //  mode 0: plain;  modes 1 (PCG step) and 2 (PCG start): skipped once the
 //  stop test has fired, one r.z partial per workgroup (and r.z_old for the
 //  Polak-Ribiere form), reduced by the next SpMV kernel.
@@ -52,14 +53,23 @@ void launch_tridiag(const Operator &op, int prec, const TriGate &g, hipStream_t 
 //  forms the increment of eq. (8) in Chebyshev form instead,
 //  d = (alpha_m - 1) d + alpha_m tau z with m = iterations done + 1
 //  (mode 4: d = tau z), skipped once the stop test has fired.
+// The x update of a solve's last iteration `iter` (the earlier ones' are the
+// SpMV's): x += alpha p, done by the mode-1 inverse launch that finds the solve
+// stopped in its own iteration.
+struct XFin {
+    double *x = nullptr;
+    const double *p = nullptr;
+    int iter = 0;
+};
 struct ZinvArgs {
-    double *zout = nullptr;
+    void *zout = nullptr;
     const double *r = nullptr;
     PcgState *state = nullptr;
     int mode = 0;
     bool pr = false;   // also reduce r.z_old (Polak-Ribiere)
     double *d = nullptr;           // modes 3, 4
     double tau = 0.0, rho2 = 0.0;  // modes 3, 4: Chebyshev parameters
+    XFin fin;                      // mode 1
 };
 void launch_zinv(const Operator &op, int prec, const ZinvArgs &a, hipStream_t s);
 
@@ -91,7 +101,7 @@ void pfused_pcg_step(Operator &op, const ZfwdArgs &fa, const TriGate &g, const Z
 void batch_tri_geom(int nr, int prec, int M, int *S, int *L, int *Lp, int *pitch, size_t *shm);
 void launch_b_init(const ProbDesc *d, int n, int rows, hipStream_t s);
 void launch_b_zero(const ProbDesc *d, int n, int rows, hipStream_t s);
-void launch_b_spmv(const ProbDesc *d, int n, int tiles, bool pr, int parity, hipStream_t s);
+void launch_b_spmv(const ProbDesc *d, int n, int tiles, int prec, bool pr, int parity, hipStream_t s);
 // Chebyshev step of every member (one workgroup per row): x += d, r -= A d,
 // ||r||^2 partials; d is the member's p0 buffer.
 void launch_b_cheb(const ProbDesc *d, int n, int rows, hipStream_t s);
@@ -104,14 +114,15 @@ struct BatchPlan {
 // Plan of a batch member with nz points per row: returns r2 and sets the rows
 // per transform workgroup.
 int batch_transform_plan(int nz, int prec, int *rows_per_wg);
-// kind 0: start (plain transform of r); 1: PCG step (alpha, x and r update,
+// kind 0: start (plain transform of r); 1: PCG step (alpha, r update,
 // transform); 2: Chebyshev step (plain transform of r, skipped once stopped).
 enum { BZ_START = 0, BZ_PCG = 1, BZ_CHEB = 2 };
-void launch_b_zfwd(const ProbDesc *d, const BatchPlan &pl, int prec, int kind, int parity, hipStream_t s);
+void launch_b_zfwd(const ProbDesc *d, const BatchPlan &pl, int prec, int kind, hipStream_t s);
 void launch_b_tridiag(const ProbDesc *d, int n, int blocks, int prec, const TriGate &g, int M, size_t shm,
                       hipStream_t s);
-// mode as for launch_zinv (1, 2: PCG; 3, 4: Chebyshev, d in each member's p0)
-void launch_b_zinv(const ProbDesc *d, const BatchPlan &pl, int prec, int mode, bool pr, hipStream_t s);
+// mode as for launch_zinv (1, 2: PCG, `iter` the iteration of mode 1; 3, 4:
+// Chebyshev, d in each member's p0)
+void launch_b_zinv(const ProbDesc *d, const BatchPlan &pl, int prec, int mode, bool pr, int iter, hipStream_t s);
 void launch_b_gather(const ProbDesc *d, int n, PcgState *out, hipStream_t s);
 // Dynamic LDS of a transform plan's workgroup; *twl: twiddles staged in LDS
 // (block-wide plans).

@@ -5,11 +5,13 @@
 // partials in the same fixed order and take the same decision, so the host
 // never waits inside an iteration and no atomics are needed:
 //   1. SpMV:    rho_k = sum(r.z partials), beta = rho_k / rho_{k-1};
-//               p = z + beta p_old (ping-pong buffers), q = A p, p.q partials
-//   2. forward: alpha = rho_k / p.q; x += alpha p, r -= alpha q, ||r||^2
-//               partials; z-transform of r
+//               x += alpha_{k-1} p_old; p = z + beta p_old (ping-pong
+//               buffers), q = A p, p.q partials
+//   2. forward: alpha_k = rho_k / p.q; r -= alpha_k q, ||r||^2 partials;
+//               z-transform of r
 //   3. r-solve: ||r||^2 -> stop test (sets `done`); r-tridiagonal solves
-//   4. inverse: inverse z-transform -> z, r.z partials
+//   4. inverse: inverse z-transform -> z, r.z partials; once the stop test has
+//               fired, x += alpha_k p instead
 // After the stop test fires, the remaining launches of the chunk return at
 // once.  The host follows the solve through a progress record that the stop
 // test publishes to pinned host memory (HostMirror), normally once per solve.
@@ -31,22 +33,28 @@ namespace {
 
 inline unsigned row_blocks(int nr) { return (unsigned)(nr < MAX_PARTIALS ? nr : MAX_PARTIALS); }
 
-template <bool PR, int RW>
-__global__ void __launch_bounds__(256)
-k_pcg_spmv(const double *__restrict__ z, const double *__restrict__ pold, double *__restrict__ pnew,
-           double *__restrict__ q, const double *__restrict__ D, const double *__restrict__ CR,
-           const double *__restrict__ CZ, int nr, int nz, PcgState *st, double *__restrict__ partials, int n_rz)
+// Waves per SIMD the SpMV is compiled for: with FP32 z two rows' loads fit 128
+// registers, the other forms would spill there.
+template <typename ZT, bool PR>
+constexpr int spmv_waves() { return (sizeof(ZT) == 4 && !PR) ? 4 : 3; }
+
+template <typename ZT, bool PR, int RW>
+__global__ void __launch_bounds__(SPMV_CHUNK / 2, (spmv_waves<ZT, PR>()))
+k_pcg_spmv(const ZT *__restrict__ z, const double *__restrict__ pold, double *__restrict__ pnew,
+           double *__restrict__ q, double *__restrict__ x, const double *__restrict__ D,
+           const double *__restrict__ CR, const double *__restrict__ CZ, int nr, int nz, PcgState *st,
+           double *__restrict__ partials, int n_rz)
 {
-    spmv_tiles<PR, RW>(z, pold, pnew, q, D, CR, CZ, nr, nz, st, partials, n_rz, blockIdx.x, gridDim.x);
+    spmv_tiles<ZT, PR, RW, SPMV_CHUNK>(z, pold, pnew, q, x, D, CR, CZ, nr, nz, st, partials, n_rz, blockIdx.x, gridDim.x);
 }
 
-// Rows per SpMV tile: 16 when that still leaves 512 tiles or more (long
+// Rows per SpMV tile: 16 when that still leaves 1024 tiles or more (long
 // windows: the halo is 2/16 of the rows), else 2 (more tiles to fill the
 // chip); the workgroups, at most MAX_PARTIALS, loop over the tiles.
 int spmv_rows(int nr, int nz)
 {
     const long nc = (nz + SPMV_CHUNK - 1) / SPMV_CHUNK;
-    return ((long)(nr / 16) * nc >= 512) ? 16 : 2;
+    return ((long)(nr / 16) * nc >= 1024) ? 16 : 2;
 }
 
 unsigned spmv_blocks(int nr, int nz)
@@ -75,10 +83,10 @@ k_pcg_init(const double *__restrict__ b, const double *__restrict__ x, double *_
 
 // ---- batched launches: one launch covers every problem of a batch --------
 // One work item (spmv.h) per workgroup.
-template <bool PR>
-__global__ void __launch_bounds__(256) k_b_spmv(const ProbDesc *__restrict__ d, int n, int parity)
+template <typename T, bool PR>
+__global__ void __launch_bounds__(SPMV_CHUNK / 2, (spmv_waves<T, PR>())) k_b_spmv(const ProbDesc *__restrict__ d, int n, int parity)
 {
-    b_spmv_item<PR>(d, n, blockIdx.x, parity);
+    b_spmv_item<T, PR, SPMV_CHUNK>(d, n, blockIdx.x, parity);
 }
 
 __global__ void __launch_bounds__(256) k_b_cheb(const ProbDesc *__restrict__ d, int n)
@@ -167,25 +175,30 @@ void launch_iteration(const SolveCtx &c, int parity, int iter)
     const unsigned gs = spmv_blocks(op.nr, op.nz);
     {
         ProfScope ps(op, c.s, AXIPCG_KERNEL_SPMV, iter, true);
-#define AXI_SPMV(PRV, RWV)                                                                                           \
-    hipExtLaunchKernelGGL((k_pcg_spmv<PRV, RWV>), dim3(gs), dim3(256), 0, c.s, ps.start(), ps.stop(), 0, op.z, pold, \
-                          pnew, op.q, op.D, op.CR, op.CZ, op.nr, op.nz, op.state, op.partials, c.n_tr)
+#define AXI_SPMV(ZT, PRV, RWV)                                                                                       \
+    hipExtLaunchKernelGGL((k_pcg_spmv<ZT, PRV, RWV>), dim3(gs), dim3(SPMV_CHUNK / 2), 0, c.s, ps.start(), ps.stop(), 0, \
+                          (const ZT *)op.z, pold, pnew, op.q, c.x, op.D, op.CR, op.CZ, op.nr, op.nz, op.state,       \
+                          op.partials, c.n_tr)
+#define AXI_SPMV_Z(PRV, RWV)                                    \
+    do {                                                        \
+        if (c.prec == AXIPCG_PREC_FP32) AXI_SPMV(float, PRV, RWV); \
+        else AXI_SPMV(double, PRV, RWV);                        \
+    } while (0)
         const bool long_tiles = spmv_rows(op.nr, op.nz) == 16;
         if (c.pr) {
-            if (long_tiles) AXI_SPMV(true, 16);
-            else AXI_SPMV(true, 2);
+            if (long_tiles) AXI_SPMV_Z(true, 16);
+            else AXI_SPMV_Z(true, 2);
         } else {
-            if (long_tiles) AXI_SPMV(false, 16);
-            else AXI_SPMV(false, 2);
+            if (long_tiles) AXI_SPMV_Z(false, 16);
+            else AXI_SPMV_Z(false, 2);
         }
+#undef AXI_SPMV_Z
 #undef AXI_SPMV
         AXI_CHECK_HIP(hipGetLastError());
     }
     ZfwdArgs fa;
     fa.fused = true;
-    fa.x = c.x;
     fa.r = op.r;
-    fa.p = pnew;
     fa.q = op.q;
     fa.state = op.state;
     fa.n_pq = (int)gs;
@@ -202,6 +215,7 @@ void launch_iteration(const SolveCtx &c, int parity, int iter)
     ia.state = op.state;
     ia.mode = 1;
     ia.pr = c.pr;
+    ia.fin = {c.x, pnew, iter};
     if (c.one) {
         // the preconditioner phases in one cooperative launch (timed as the
         // forward-transform class)
@@ -453,10 +467,17 @@ int cheb_solve_impl(Operator &op, const double *b, double *x, double gamma1, dou
 
 }  // namespace
 
-void launch_b_spmv(const ProbDesc *d, int n, int tiles, bool pr, int parity, hipStream_t s)
+void launch_b_spmv(const ProbDesc *d, int n, int tiles, int prec, bool pr, int parity, hipStream_t s)
 {
-    if (pr) hipLaunchKernelGGL(k_b_spmv<true>, dim3(tiles), dim3(256), 0, s, d, n, parity);
-    else hipLaunchKernelGGL(k_b_spmv<false>, dim3(tiles), dim3(256), 0, s, d, n, parity);
+#define AXI_BSPMV(T, PRV) hipLaunchKernelGGL((k_b_spmv<T, PRV>), dim3(tiles), dim3(SPMV_CHUNK / 2), 0, s, d, n, parity)
+    if (prec == AXIPCG_PREC_FP32) {
+        if (pr) AXI_BSPMV(float, true);
+        else AXI_BSPMV(float, false);
+    } else {
+        if (pr) AXI_BSPMV(double, true);
+        else AXI_BSPMV(double, false);
+    }
+#undef AXI_BSPMV
     AXI_CHECK_HIP(hipGetLastError());
 }
 

@@ -16,7 +16,7 @@
 //  phase 3  back substitution from X_{s-1}, X_s; inverse transform to z
 //
 // Used for FP32 standalone applies (plain transform) and for the PCG
-// iteration (the x, r update fused into phase 1, ||r||^2 and r.z partials as
+// iteration (the r update fused into phase 1, ||r||^2 and r.z partials as
 // in the three launches), when the strips fit the chip at once.
 //
 // Grid barriers (gridbar.h).  Barrier numbers come from a per-handle launch
@@ -32,16 +32,17 @@ namespace {
 
 template <typename T>
 struct OneArgs {
-    // phase 1: plain (rin) or the PCG step (x, r, p, q, p.q partials)
+    // phase 1: plain (rin) or the PCG step (r, q, p.q partials)
     const double *rin;
-    double *x, *r;
-    const double *p, *q;
+    double *r;
+    const double *q;
     PcgState *st;
     double *partials;
     int n_pq;
     T *red_e, *red_g, *red_x;
     TriGate g;             // phase 2: stop test (mode 1) or none (mode 0)
-    double *zout;          // phase 3
+    void *zout;            // phase 3
+    XFin fin;
     const typename vec2_of<T>::type *tw, *pt;
     Lines<T> ln;
     int nr, G, mpw;
@@ -51,7 +52,7 @@ struct OneArgs {
 };
 
 // KIND 0: standalone apply (plain transform, no gate, z out);
-// KIND 1: PCG iteration (x, r update, stop test, z and r.z partials).
+// KIND 1: PCG iteration (r update, stop test, z and r.z partials).
 template <typename T, int BC, int KIND, int R2, int R>
 __global__ void __launch_bounds__(64 * R) k_strip_one(OneArgs<T> A)
 {
@@ -65,20 +66,25 @@ __global__ void __launch_bounds__(64 * R) k_strip_one(OneArgs<T> A)
     T *tile = reinterpret_cast<T *>(smem_raw);
     T *base2 = tile + R * PITCH;
     const int s = blockIdx.x;
+    using Z = ZOut<T, PCG ? 1 : 0>;
+    Z *zout = static_cast<Z *>(A.zout);
     auto fail = [&]() {
         if (threadIdx.x == 0) {
             __hip_atomic_store(A.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (PCG) A.st->done = ST_BREAK;
         }
-        for (int e = threadIdx.x; e < R * N; e += blockDim.x) A.zout[(size_t)s * R * N + e] = __builtin_nan("");
+        for (int e = threadIdx.x; e < R * N; e += blockDim.x) zout[(size_t)s * R * N + e] = (Z)__builtin_nan("");
     };
     // every workgroup reaches the same verdict (the stop flag and p.q are
     // read or summed identically), so either all continue or all return
-    if (!strip_phase1<T, BC, PCG, R2, R>(A.rin, A.x, A.r, A.p, A.q, A.st, A.partials, A.n_pq, nullptr, A.red_e,
+    if (!strip_phase1<T, BC, PCG, R2, R>(A.rin, A.r, A.q, A.st, A.partials, A.n_pq, nullptr, A.red_e,
                                          A.red_g, A.tw, A.pt, A.ln, A.nr, s, tile))
         return;
     if (!grid_sync(A.bar, A.G, 2u * A.epoch + 1u, &flag)) return fail();
-    if (PCG && tridiag_gate(A.st, A.partials, A.g, red, s) != ST_RUN) return;
+    if (PCG && tridiag_gate(A.st, A.partials, A.g, red, s) != ST_RUN) {
+        x_finish(A.fin, A.st, (size_t)s * R * N, R * N, threadIdx.x, blockDim.x);
+        return;
+    }
     const int l0 = s * A.mpw, cnt = N - l0 < A.mpw ? N - l0 : A.mpw;
     if (cnt > 0) {
         strip_stage2<T, false>(A.red_e, A.red_g, A.ln, A.nr, N, A.G, l0, cnt, base2);
@@ -86,7 +92,7 @@ __global__ void __launch_bounds__(64 * R) k_strip_one(OneArgs<T> A)
         strip_solve2<T, R, LMAX, false>(A.red_x, A.ln, A.nr, N, A.G, l0, cnt, base2);
     }
     if (!grid_sync(A.bar, A.G, 2u * A.epoch + 2u, &flag)) return fail();
-    strip_phase3<T, BC, PCG ? 1 : 0, R2, R>(nullptr, A.red_x, A.zout, A.r, A.st, A.partials, false, A.tw, A.pt,
+    strip_phase3<T, BC, PCG ? 1 : 0, R2, R>(nullptr, A.red_x, zout, A.r, A.st, A.partials, false, A.tw, A.pt,
                                             A.ln, A.nr, nullptr, 0.0, 0.0, s, tile);
 }
 
@@ -188,9 +194,8 @@ void pfused_pcg_step(Operator &op, const ZfwdArgs &fa, const TriGate &g, const Z
 {
     const PfPlan &pl = op.pf[1];
     OneArgs<float> a = one_args(op, pl);
-    a.x = fa.x;
     a.r = fa.r;
-    a.p = fa.p;
+    a.fin = ia.fin;
     a.q = fa.q;
     a.st = fa.state;
     a.partials = op.partials;

@@ -12,30 +12,28 @@ namespace {
 // (512 threads for N = 4096, 256 or fewer below)
 template <typename T, int BC, bool FUSED, bool TWLDS, int ROWS>
 __global__ void __launch_bounds__(512)
-k_zfwd(const double *__restrict__ rin, double *__restrict__ x, double *__restrict__ r,
-       const double *__restrict__ p, const double *__restrict__ q, PcgState *st,
+k_zfwd(const double *__restrict__ rin, double *__restrict__ r, const double *__restrict__ q, PcgState *st,
        double *__restrict__ partials, int n_pq,
        T *__restrict__ spec, const typename vec2_of<T>::type *__restrict__ tw,
        const typename vec2_of<T>::type *__restrict__ pt, int nr, int N)
 {
-    zfwd_body<T, BC, FUSED, TWLDS, ROWS>(rin, x, r, p, q, st, partials, n_pq, spec, tw, pt, nr, N, blockIdx.x);
+    zfwd_body<T, BC, FUSED, TWLDS, ROWS>(rin, r, q, st, partials, n_pq, spec, tw, pt, nr, N, blockIdx.x);
 }
 
 template <typename T, int BC, int MODE, bool TWLDS, int ROWS>
 __global__ void __launch_bounds__(512)
-k_zinv(const T *__restrict__ spec, double *__restrict__ zout, const double *__restrict__ r,
+k_zinv(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout, const double *__restrict__ r,
        const PcgState *st, double *__restrict__ partials, bool pr,
        const typename vec2_of<T>::type *__restrict__ tw,
        const typename vec2_of<T>::type *__restrict__ pt, int nr, int N, double *__restrict__ dinc, double tau,
-       double rho2)
+       double rho2, XFin fin)
 {
-    zinv_body<T, BC, MODE, TWLDS, ROWS>(spec, zout, r, st, partials, pr, tw, pt, nr, N, blockIdx.x, dinc, tau, rho2);
+    zinv_body<T, BC, MODE, TWLDS, ROWS>(spec, zout, r, st, partials, pr, tw, pt, nr, N, blockIdx.x, dinc, tau, rho2, fin);
 }
 
 template <typename T, int BC, bool FUSED, int R2>
 __global__ void __launch_bounds__(256)
-k_zfwd_w(const double *__restrict__ rin, double *__restrict__ x, double *__restrict__ r,
-         const double *__restrict__ p, const double *__restrict__ q, PcgState *st,
+k_zfwd_w(const double *__restrict__ rin, double *__restrict__ r, const double *__restrict__ q, PcgState *st,
          double *__restrict__ partials, int n_pq, T *__restrict__ spec,
          const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt,
          int nr)
@@ -43,20 +41,21 @@ k_zfwd_w(const double *__restrict__ rin, double *__restrict__ x, double *__restr
     constexpr int WR = wave_rows<T, R2>();
     const int row = blockIdx.x * WR + (threadIdx.x >> 6);
     RowStore<T> out{spec + (size_t)(row < nr ? row : 0) * wfft::Geo<R2>::N};
-    zfwd_w_body<T, BC, FUSED, R2>(rin, x, r, p, q, st, partials, n_pq, tw, pt, nr, row, blockIdx.x, out);
+    zfwd_w_body<T, BC, FUSED, R2>(rin, r, q, st, partials, n_pq, tw, pt, nr, row, blockIdx.x, out);
 }
 
 template <typename T, int BC, int MODE, int R2>
 __global__ void __launch_bounds__(256)
-k_zinv_w(const T *__restrict__ spec, double *__restrict__ zout, const double *__restrict__ r,
+k_zinv_w(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout, const double *__restrict__ r,
          const PcgState *st, double *__restrict__ partials, bool pr,
          const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt,
-         int nr, double *__restrict__ dinc, double tau, double rho2)
+         int nr, double *__restrict__ dinc, double tau, double rho2, XFin fin)
 {
     constexpr int WR = wave_rows<T, R2>();
     const int row = blockIdx.x * WR + (threadIdx.x >> 6);
     RowLoad<T> in{spec + (size_t)(row < nr ? row : nr - 1) * wfft::Geo<R2>::N};
-    zinv_w_body<T, BC, MODE, R2>(in, zout, r, st, partials, pr, tw, pt, nr, dinc, tau, rho2, row, blockIdx.x);
+    zinv_w_body<T, BC, MODE, R2>(in, zout, r, st, partials, pr, tw, pt, nr, dinc, tau, rho2, row, blockIdx.x, nullptr,
+                                   fin);
 }
 
 // Threads of an r-solve workgroup (one wave per mode): up to eight FP32 modes
@@ -79,15 +78,15 @@ k_tridiag(T *__restrict__ spec, const T *__restrict__ cb_g, const T *__restrict_
 // problems of that plan, with tr_start counted within the launch.  One work
 // item (xform.h) per workgroup.
 template <typename T, int KIND, bool TWLDS>
-__global__ void __launch_bounds__(256) k_b_zfwd(const ProbDesc *__restrict__ d, int n, int parity)
+__global__ void __launch_bounds__(256) k_b_zfwd(const ProbDesc *__restrict__ d, int n)
 {
-    b_zfwd_item<T, KIND == BZ_PCG, TWLDS, false, KIND == BZ_CHEB>(d, n, blockIdx.x, parity);
+    b_zfwd_item<T, KIND == BZ_PCG, TWLDS, false, KIND == BZ_CHEB>(d, n, blockIdx.x);
 }
 
 template <typename T, int MODE, bool TWLDS>
-__global__ void __launch_bounds__(256) k_b_zinv(const ProbDesc *__restrict__ d, int n, bool pr)
+__global__ void __launch_bounds__(256) k_b_zinv(const ProbDesc *__restrict__ d, int n, bool pr, int iter)
 {
-    b_zinv_item<T, MODE, TWLDS>(d, n, blockIdx.x, pr);
+    b_zinv_item<T, MODE, TWLDS>(d, n, blockIdx.x, pr, iter);
 }
 
 // Two waves per SIMD for the FP32 plans up to rows of 1024 points: the fused
@@ -97,15 +96,15 @@ template <typename T, int R2>
 constexpr int bzw_waves() { return (sizeof(T) == 4 && R2 <= 8) ? 2 : 1; }
 
 template <typename T, int KIND, int R2>
-__global__ void __launch_bounds__(256, (bzw_waves<T, R2>())) k_b_zfwd_w(const ProbDesc *__restrict__ d, int n, int parity)
+__global__ void __launch_bounds__(256, (bzw_waves<T, R2>())) k_b_zfwd_w(const ProbDesc *__restrict__ d, int n)
 {
-    b_zfwd_w_item<T, KIND == BZ_PCG, R2, false, KIND == BZ_CHEB>(d, n, blockIdx.x, parity);
+    b_zfwd_w_item<T, KIND == BZ_PCG, R2, false, KIND == BZ_CHEB>(d, n, blockIdx.x);
 }
 
 template <typename T, int MODE, int R2>
-__global__ void __launch_bounds__(256) k_b_zinv_w(const ProbDesc *__restrict__ d, int n, bool pr)
+__global__ void __launch_bounds__(256) k_b_zinv_w(const ProbDesc *__restrict__ d, int n, bool pr, int iter)
 {
-    b_zinv_w_item<T, MODE, R2>(d, n, blockIdx.x, pr);
+    b_zinv_w_item<T, MODE, R2>(d, n, blockIdx.x, pr, iter);
 }
 
 template <typename T>
@@ -168,11 +167,9 @@ void zfwd_ttr(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     allow_transform_lds(reinterpret_cast<const void *>(&k_zfwd<T, BC, true, TWL, ROWS>), shm, lds_set[0]);
     allow_transform_lds(reinterpret_cast<const void *>(&k_zfwd<T, BC, false, TWL, ROWS>), shm, lds_set[1]);
     if (a.fused)
-        hipLaunchKernelGGL((k_zfwd<T, BC, true, TWL, ROWS>), grid, dim3(thr), shm, s, nullptr, a.x, a.r, a.p, a.q,
-                           a.state, op.partials, a.n_pq, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
+        hipLaunchKernelGGL((k_zfwd<T, BC, true, TWL, ROWS>), grid, dim3(thr), shm, s, nullptr, a.r, a.q, a.state, op.partials, a.n_pq, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
     else
-        hipLaunchKernelGGL((k_zfwd<T, BC, false, TWL, ROWS>), grid, dim3(thr), shm, s, a.rin, nullptr, nullptr,
-                           nullptr, nullptr, a.state, op.partials, 0, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
+        hipLaunchKernelGGL((k_zfwd<T, BC, false, TWL, ROWS>), grid, dim3(thr), shm, s, a.rin, nullptr, nullptr, a.state, op.partials, 0, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
     AXI_CHECK_HIP(hipGetLastError());
 }
 
@@ -198,11 +195,10 @@ void zfwd_wave(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     const dim3 grid((op.nr + WR - 1) / WR), block(64 * WR);
     const size_t shm = (size_t)WR * wfft::Geo<R2>::LB * sizeof(cx<T>);
     if (a.fused)
-        hipLaunchKernelGGL((k_zfwd_w<T, BC, true, R2>), grid, block, shm, s, nullptr, a.x, a.r, a.p, a.q, a.state,
+        hipLaunchKernelGGL((k_zfwd_w<T, BC, true, R2>), grid, block, shm, s, nullptr, a.r, a.q, a.state,
                            op.partials, a.n_pq, (T *)op.spec, tb.tw, tb.pt, op.nr);
     else
-        hipLaunchKernelGGL((k_zfwd_w<T, BC, false, R2>), grid, block, shm, s, a.rin, nullptr, nullptr, nullptr,
-                           nullptr, a.state, op.partials, 0, (T *)op.spec, tb.tw, tb.pt, op.nr);
+        hipLaunchKernelGGL((k_zfwd_w<T, BC, false, R2>), grid, block, shm, s, a.rin, nullptr, nullptr, a.state, op.partials, 0, (T *)op.spec, tb.tw, tb.pt, op.nr);
     AXI_CHECK_HIP(hipGetLastError());
 }
 
@@ -244,24 +240,24 @@ void zinv_ttr(const Operator &op, const ZinvArgs &a, hipStream_t s)
     allow_transform_lds(reinterpret_cast<const void *>(&k_zinv<T, BC, 4, TWL, ROWS>), shm, lds_set[4]);
     switch (a.mode) {
     case 0:
-        hipLaunchKernelGGL((k_zinv<T, BC, 0, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, a.zout,
-                           nullptr, nullptr, op.partials, false, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0);
+        hipLaunchKernelGGL((k_zinv<T, BC, 0, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 0> *)a.zout,
+                           nullptr, nullptr, op.partials, false, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0, a.fin);
         break;
     case 1:
-        hipLaunchKernelGGL((k_zinv<T, BC, 1, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, a.zout,
-                           a.r, a.state, op.partials, a.pr, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0);
+        hipLaunchKernelGGL((k_zinv<T, BC, 1, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 1> *)a.zout,
+                           a.r, a.state, op.partials, a.pr, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0, a.fin);
         break;
     case 2:
-        hipLaunchKernelGGL((k_zinv<T, BC, 2, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, a.zout,
-                           a.r, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0);
+        hipLaunchKernelGGL((k_zinv<T, BC, 2, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 2> *)a.zout,
+                           a.r, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0, a.fin);
         break;
     case 3:
         hipLaunchKernelGGL((k_zinv<T, BC, 3, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, nullptr,
-                           nullptr, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, a.d, a.tau, a.rho2);
+                           nullptr, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, a.d, a.tau, a.rho2, a.fin);
         break;
     default:
         hipLaunchKernelGGL((k_zinv<T, BC, 4, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, nullptr,
-                           nullptr, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, a.d, a.tau, a.rho2);
+                           nullptr, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, a.d, a.tau, a.rho2, a.fin);
         break;
     }
     AXI_CHECK_HIP(hipGetLastError());
@@ -277,24 +273,24 @@ void zinv_wave(const Operator &op, const ZinvArgs &a, hipStream_t s)
     const T *spec = (const T *)op.spec;
     switch (a.mode) {
     case 0:
-        hipLaunchKernelGGL((k_zinv_w<T, BC, 0, R2>), grid, block, shm, s, spec, a.zout, nullptr, nullptr,
-                           op.partials, false, tb.tw, tb.pt, op.nr, nullptr, 0.0, 0.0);
+        hipLaunchKernelGGL((k_zinv_w<T, BC, 0, R2>), grid, block, shm, s, spec, (ZOut<T, 0> *)a.zout, nullptr, nullptr,
+                           op.partials, false, tb.tw, tb.pt, op.nr, nullptr, 0.0, 0.0, a.fin);
         break;
     case 1:
-        hipLaunchKernelGGL((k_zinv_w<T, BC, 1, R2>), grid, block, shm, s, spec, a.zout, a.r, a.state, op.partials,
-                           a.pr, tb.tw, tb.pt, op.nr, nullptr, 0.0, 0.0);
+        hipLaunchKernelGGL((k_zinv_w<T, BC, 1, R2>), grid, block, shm, s, spec, (ZOut<T, 1> *)a.zout, a.r, a.state, op.partials,
+                           a.pr, tb.tw, tb.pt, op.nr, nullptr, 0.0, 0.0, a.fin);
         break;
     case 2:
-        hipLaunchKernelGGL((k_zinv_w<T, BC, 2, R2>), grid, block, shm, s, spec, a.zout, a.r, a.state, op.partials,
-                           false, tb.tw, tb.pt, op.nr, nullptr, 0.0, 0.0);
+        hipLaunchKernelGGL((k_zinv_w<T, BC, 2, R2>), grid, block, shm, s, spec, (ZOut<T, 2> *)a.zout, a.r, a.state, op.partials,
+                           false, tb.tw, tb.pt, op.nr, nullptr, 0.0, 0.0, a.fin);
         break;
     case 3:
         hipLaunchKernelGGL((k_zinv_w<T, BC, 3, R2>), grid, block, shm, s, spec, nullptr, nullptr, a.state,
-                           op.partials, false, tb.tw, tb.pt, op.nr, a.d, a.tau, a.rho2);
+                           op.partials, false, tb.tw, tb.pt, op.nr, a.d, a.tau, a.rho2, a.fin);
         break;
     default:
         hipLaunchKernelGGL((k_zinv_w<T, BC, 4, R2>), grid, block, shm, s, spec, nullptr, nullptr, a.state,
-                           op.partials, false, tb.tw, tb.pt, op.nr, a.d, a.tau, a.rho2);
+                           op.partials, false, tb.tw, tb.pt, op.nr, a.d, a.tau, a.rho2, a.fin);
         break;
     }
     AXI_CHECK_HIP(hipGetLastError());
@@ -442,11 +438,11 @@ int batch_transform_plan(int nz, int prec, int *rows_per_wg)
 }
 
 template <typename T, int R2>
-void b_zfwd_wave(const ProbDesc *d, const BatchPlan &pl, int kind, int parity, hipStream_t s)
+void b_zfwd_wave(const ProbDesc *d, const BatchPlan &pl, int kind, hipStream_t s)
 {
     constexpr int WR = wave_rows<T, R2>();
     const size_t shm = (size_t)WR * wfft::Geo<R2>::LB * sizeof(cx<T>);
-#define AXI_BZW(K) hipLaunchKernelGGL((k_b_zfwd_w<T, K, R2>), dim3(pl.blocks), dim3(64 * WR), shm, s, d + pl.off, pl.n, parity)
+#define AXI_BZW(K) hipLaunchKernelGGL((k_b_zfwd_w<T, K, R2>), dim3(pl.blocks), dim3(64 * WR), shm, s, d + pl.off, pl.n)
     if (kind == BZ_PCG) AXI_BZW(BZ_PCG);
     else if (kind == BZ_CHEB) AXI_BZW(BZ_CHEB);
     else AXI_BZW(BZ_START);
@@ -454,11 +450,11 @@ void b_zfwd_wave(const ProbDesc *d, const BatchPlan &pl, int kind, int parity, h
 }
 
 template <typename T, int R2>
-void b_zinv_wave(const ProbDesc *d, const BatchPlan &pl, int mode, bool pr, hipStream_t s)
+void b_zinv_wave(const ProbDesc *d, const BatchPlan &pl, int mode, bool pr, int iter, hipStream_t s)
 {
     constexpr int WR = wave_rows<T, R2>();
     const size_t shm = (size_t)WR * wfft::Geo<R2>::LB * sizeof(cx<T>);
-#define AXI_BIW(MD) hipLaunchKernelGGL((k_b_zinv_w<T, MD, R2>), dim3(pl.blocks), dim3(64 * WR), shm, s, d + pl.off, pl.n, pr)
+#define AXI_BIW(MD) hipLaunchKernelGGL((k_b_zinv_w<T, MD, R2>), dim3(pl.blocks), dim3(64 * WR), shm, s, d + pl.off, pl.n, pr, iter)
     switch (mode) {
     case 1: AXI_BIW(1); break;
     case 2: AXI_BIW(2); break;
@@ -469,21 +465,21 @@ void b_zinv_wave(const ProbDesc *d, const BatchPlan &pl, int mode, bool pr, hipS
 }
 
 template <typename T>
-void b_zfwd_t(const ProbDesc *d, const BatchPlan &pl, int kind, int parity, hipStream_t s)
+void b_zfwd_t(const ProbDesc *d, const BatchPlan &pl, int kind, hipStream_t s)
 {
     switch (pl.r2) {
-    case 2: b_zfwd_wave<T, 2>(d, pl, kind, parity, s); break;
-    case 4: b_zfwd_wave<T, 4>(d, pl, kind, parity, s); break;
-    case 8: b_zfwd_wave<T, 8>(d, pl, kind, parity, s); break;
+    case 2: b_zfwd_wave<T, 2>(d, pl, kind, s); break;
+    case 4: b_zfwd_wave<T, 4>(d, pl, kind, s); break;
+    case 8: b_zfwd_wave<T, 8>(d, pl, kind, s); break;
     case 16:
-        if constexpr (sizeof(T) == 4) b_zfwd_wave<T, 16>(d, pl, kind, parity, s);
+        if constexpr (sizeof(T) == 4) b_zfwd_wave<T, 16>(d, pl, kind, s);
         else AXI_REQUIRE(false, "no one-wave FP64 plan for N = 2048");
         break;
     default: {
         const size_t shm = transform_lds<T>(pl.nz_max);
         const dim3 grid(pl.blocks), block(256);
         const ProbDesc *dp = d + pl.off;
-#define AXI_BZF(K, TW) hipLaunchKernelGGL((k_b_zfwd<T, K, TW>), grid, block, shm, s, dp, pl.n, parity)
+#define AXI_BZF(K, TW) hipLaunchKernelGGL((k_b_zfwd<T, K, TW>), grid, block, shm, s, dp, pl.n)
         if (twiddles_in_lds<T>(pl.nz_max)) {
             if (kind == BZ_PCG) AXI_BZF(BZ_PCG, true);
             else if (kind == BZ_CHEB) AXI_BZF(BZ_CHEB, true);
@@ -500,14 +496,14 @@ void b_zfwd_t(const ProbDesc *d, const BatchPlan &pl, int kind, int parity, hipS
 }
 
 template <typename T>
-void b_zinv_t(const ProbDesc *d, const BatchPlan &pl, int mode, bool pr, hipStream_t s)
+void b_zinv_t(const ProbDesc *d, const BatchPlan &pl, int mode, bool pr, int iter, hipStream_t s)
 {
     switch (pl.r2) {
-    case 2: b_zinv_wave<T, 2>(d, pl, mode, pr, s); break;
-    case 4: b_zinv_wave<T, 4>(d, pl, mode, pr, s); break;
-    case 8: b_zinv_wave<T, 8>(d, pl, mode, pr, s); break;
+    case 2: b_zinv_wave<T, 2>(d, pl, mode, pr, iter, s); break;
+    case 4: b_zinv_wave<T, 4>(d, pl, mode, pr, iter, s); break;
+    case 8: b_zinv_wave<T, 8>(d, pl, mode, pr, iter, s); break;
     case 16:
-        if constexpr (sizeof(T) == 4) b_zinv_wave<T, 16>(d, pl, mode, pr, s);
+        if constexpr (sizeof(T) == 4) b_zinv_wave<T, 16>(d, pl, mode, pr, iter, s);
         else AXI_REQUIRE(false, "no one-wave FP64 plan for N = 2048");
         break;
     default: {
@@ -515,7 +511,7 @@ void b_zinv_t(const ProbDesc *d, const BatchPlan &pl, int mode, bool pr, hipStre
         const bool twl = twiddles_in_lds<T>(pl.nz_max);
         const dim3 grid(pl.blocks), block(256);
         const ProbDesc *dp = d + pl.off;
-#define AXI_BZI(MD, TW) hipLaunchKernelGGL((k_b_zinv<T, MD, TW>), grid, block, shm, s, dp, pl.n, pr)
+#define AXI_BZI(MD, TW) hipLaunchKernelGGL((k_b_zinv<T, MD, TW>), grid, block, shm, s, dp, pl.n, pr, iter)
 #define AXI_BZI2(MD) do { if (twl) AXI_BZI(MD, true); else AXI_BZI(MD, false); } while (0)
         switch (mode) {
         case 1: AXI_BZI2(1); break;
@@ -530,17 +526,17 @@ void b_zinv_t(const ProbDesc *d, const BatchPlan &pl, int mode, bool pr, hipStre
     AXI_CHECK_HIP(hipGetLastError());
 }
 
-void launch_b_zfwd(const ProbDesc *d, const BatchPlan &pl, int prec, int kind, int parity, hipStream_t s)
+void launch_b_zfwd(const ProbDesc *d, const BatchPlan &pl, int prec, int kind, hipStream_t s)
 {
-    if (prec == AXIPCG_PREC_FP32) b_zfwd_t<float>(d, pl, kind, parity, s);
-    else b_zfwd_t<double>(d, pl, kind, parity, s);
+    if (prec == AXIPCG_PREC_FP32) b_zfwd_t<float>(d, pl, kind, s);
+    else b_zfwd_t<double>(d, pl, kind, s);
 }
 
-void launch_b_zinv(const ProbDesc *d, const BatchPlan &pl, int prec, int mode, bool pr, hipStream_t s)
+void launch_b_zinv(const ProbDesc *d, const BatchPlan &pl, int prec, int mode, bool pr, int iter, hipStream_t s)
 {
     AXI_REQUIRE(mode >= 1 && mode <= 4, "batched inverse transform mode must be 1..4");
-    if (prec == AXIPCG_PREC_FP32) b_zinv_t<float>(d, pl, mode, pr, s);
-    else b_zinv_t<double>(d, pl, mode, pr, s);
+    if (prec == AXIPCG_PREC_FP32) b_zinv_t<float>(d, pl, mode, pr, iter, s);
+    else b_zinv_t<double>(d, pl, mode, pr, iter, s);
 }
 
 void launch_b_tridiag(const ProbDesc *d, int n, int blocks, int prec, const TriGate &g, int M, size_t shm,

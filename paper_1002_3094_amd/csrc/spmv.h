@@ -28,6 +28,11 @@ struct Pair { double a, b; };
 
 __device__ inline Pair ld2(const double *p) { const double2 v = *reinterpret_cast<const double2 *>(p); return {v.x, v.y}; }
 
+// A pair of z in its own type (kept so in registers until it is used).
+template <typename ZT> struct ZPair { ZT a, b; };
+__device__ inline ZPair<double> ldz(const double *p) { const double2 v = *reinterpret_cast<const double2 *>(p); return {v.x, v.y}; }
+__device__ inline ZPair<float> ldz(const float *p) { const float2 v = *reinterpret_cast<const float2 *>(p); return {v.x, v.y}; }
+
 // (A v) at the pair (e, e+1) of row i, columns k, k+1 (k even, k + 1 < nz)
 __device__ inline Pair stencil2(const double *__restrict__ v, const double *__restrict__ D,
                                 const double *__restrict__ CR, const double *__restrict__ CZ, size_t e, int i, int k,
@@ -59,76 +64,126 @@ __device__ inline Pair stencil2(const double *__restrict__ v, const double *__re
 // p_old is the same product up to rounding (no recurrence: both terms are
 // recomputed from the stored vectors every iteration).
 //
+// The x update of the previous iteration rides along: x += alpha p_old reads
+// the p_old that the sweep holds anyway, where the forward kernel would read p
+// for it alone (8 bytes a point less per iteration).  The step length of a
+// solve's last iteration is applied by the inverse launch that finds the solve
+// stopped (XFin).
+//
 // It runs on tiles of RW consecutive rows by
-// SPMV_CHUNK columns: a thread owns one column pair and sweeps the tile's
+// CHUNK columns: a thread owns one column pair and sweeps the tile's
 // rows with a three-row window of z and p_old in registers (each row is
 // loaded once per tile, plus one halo row above and below), and the
 // z-neighbours k - 1, k + 2 (and the coupling CZ[k - 1]) come from the
-// adjacent lanes, with loads only at the wave's edges.  The stencil's
+// adjacent lanes, with loads only at the wave's edges.  Each row's loads are
+// issued one row ahead (the first two rows' ahead of the reduction of the r.z
+// partials), so that a tile waits for memory about once.  The stencil's
 // arithmetic is that of stencil2, term for term.  Tiles are dealt to the
 // XCDs in contiguous runs (xcd_swizzle), so a tile's halo rows are the
 // neighbouring tiles' rows in the same L2.  The tiles t = vb, vb + vnb, ...
 // of the nb * nc of the problem; one p.q partial, in slot vb.
-constexpr int SPMV_CHUNK = 512;   // columns per tile: 256 threads x one pair
+// Columns per tile, CHUNK = twice the workgroup's threads: two waves and 256
+// columns (SPMV_CHUNK), so that a large grid's workgroups come and go in
+// smaller pieces while others load (1024^2 FP32, 2-row tiles: 14.8 us against
+// 15.3 with 512 columns, 64-problem batch tiles 112 against 122 us); the
+// single-launch batch's workgroups of 256 threads take 512 (BATCH_ONE_CHUNK).
+constexpr int SPMV_CHUNK = 256;
+constexpr int BATCH_ONE_CHUNK = 512;
 
-template <bool PR, int RW>
-__device__ __forceinline__ void spmv_tiles(const double *__restrict__ z, const double *__restrict__ pold,
-                                           double *__restrict__ pnew, double *__restrict__ q,
+// z comes in the preconditioner's own type ZT: an FP32 preconditioner's z
+// holds float values, so as floats it is the same vector in half the bytes.
+// With the x update here and z so, an FP32 iteration moves 114 bytes a point
+// instead of 130: 541 against 594 us at 4096^2 (SpMV 195 -> 222, forward
+// 207 -> 150, inverse 119 -> 105), 25.5 against 26.9 us for SpMV and forward
+// at 1024^2, 7.5 against 8.5 ms for 24 uneven problems.
+template <typename ZT, bool PR, int RW, int CHUNK>
+__device__ __forceinline__ void spmv_tiles(const ZT *__restrict__ z, const double *__restrict__ pold,
+                                           double *__restrict__ pnew, double *__restrict__ q, double *__restrict__ x,
                                            const double *__restrict__ D, const double *__restrict__ CR,
                                            const double *__restrict__ CZ, int nr, int nz, PcgState *st,
                                            double *__restrict__ partials, int n_rz, int vb, int vnb)
 {
     __shared__ double red[8];
-    double acc = 0.0, beta = 0.0;
+    double acc = 0.0, beta = 0.0, aprev = 0.0;
     bool have_beta = false;
     int k_it = 0;
-    const int nb = (nr + RW - 1) / RW, nc = (nz + SPMV_CHUNK - 1) / SPMV_CHUNK;
+    const int nb = (nr + RW - 1) / RW, nc = (nz + CHUNK - 1) / CHUNK;
     const int lane = threadIdx.x & 63;
     // the first round of the r.z partials, issued ahead of the first tile's
     // rows so that the two reads are in flight together (not in the
     // Polak-Ribiere form, whose second sum would cost it a wave per SIMD)
-    TotalLoads rz_pre;
+    TotalLoads<2> rz_pre;
     if constexpr (!PR) total_issue(partials + SLOT_RZ * MAX_PARTIALS, n_rz, rz_pre);
     for (int t = vb; t < nb * nc; t += vnb) {
         const int item = xcd_swizzle(t, nb * nc);
         const int i0 = RW * (item / nc);
-        const int k = (item % nc) * SPMV_CHUNK + 2 * (int)threadIdx.x;
+        const int k = (item % nc) * CHUNK + 2 * (int)threadIdx.x;
         const bool in = k < nz;
+        const bool le = lane == 0 && in && k > 0, re = lane == 63 && in && k + 2 < nz;
+        // what row i needs beyond the window: z, p_old of row i + 1, and its
+        // own coefficients, x and (at the wave's edges) outer neighbours
+        struct Row {
+            ZPair<ZT> z;
+            Pair p, cr, d, cz, x;
+            ZT ez;
+            double ep, ecz;
+        };
+        auto load = [&](int i, Row &w) {
+            const Pair none{0.0, 0.0};
+            const size_t e = (size_t)i * nz + k;
+            const bool row = in && i < nr, up = in && i + 1 < nr;
+            w.z = up ? ldz(z + e + nz) : ZPair<ZT>{0, 0};
+            w.p = up ? ld2(pold + e + nz) : none;
+            w.cr = up ? ld2(CR + e) : none;
+            w.d = row ? ld2(D + e) : none;
+            w.cz = row ? ld2(CZ + e) : none;
+            w.x = row ? ld2(x + e) : none;
+            w.ez = 0;
+            w.ep = w.ecz = 0.0;
+            if ((le || re) && i < nr) {
+                const size_t n = le ? e - 1 : e + 2;
+                w.ez = z[n];
+                w.ep = pold[n];
+                w.ecz = CZ[n];   // used at the left edge only
+            }
+        };
         // window: [0] row i - 1, [1] row i, [2] row i + 1; crm = CR of row i - 1
-        Pair zw[3], pw[3], crm;
+        ZPair<ZT> zw[3];
+        Pair pw[3], crm;
         {
             const size_t e = (size_t)i0 * nz + k;
             const bool dn = in && i0 > 0;
-            zw[0] = dn ? ld2(z + e - nz) : Pair{0.0, 0.0};
+            zw[0] = dn ? ldz(z + e - nz) : ZPair<ZT>{0, 0};
             pw[0] = dn ? ld2(pold + e - nz) : Pair{0.0, 0.0};
             crm = dn ? ld2(CR + e - nz) : Pair{0.0, 0.0};
-            zw[1] = in ? ld2(z + e) : Pair{0.0, 0.0};
+            zw[1] = in ? ldz(z + e) : ZPair<ZT>{0, 0};
             pw[1] = in ? ld2(pold + e) : Pair{0.0, 0.0};
         }
+        Row cur, nxt;
+        load(i0, cur);
 #pragma unroll
         for (int rr = 0; rr < RW; ++rr) {
             const int i = i0 + rr;
             if (i >= nr) break;
             const bool up = i + 1 < nr;
             const size_t e = (size_t)i * nz + k;
-            zw[2] = (in && up) ? ld2(z + e + nz) : Pair{0.0, 0.0};
-            pw[2] = (in && up) ? ld2(pold + e + nz) : Pair{0.0, 0.0};
-            const Pair cr = (in && up) ? ld2(CR + e) : Pair{0.0, 0.0};
-            const Pair d = in ? ld2(D + e) : Pair{0.0, 0.0};
-            const Pair cz = in ? ld2(CZ + e) : Pair{0.0, 0.0};
+            if (rr + 1 < RW) load(i + 1, nxt);
+            zw[2] = cur.z;
+            pw[2] = cur.p;
+            const Pair cr = cur.cr, d = cur.d, cz = cur.cz;
             // every lane takes part in the shuffles (lanes past nz hold zeros)
-            double zl = __shfl_up(zw[1].b, 1), pl = __shfl_up(pw[1].b, 1), czl = __shfl_up(cz.b, 1);
-            double zr = __shfl_down(zw[1].a, 1), pr = __shfl_down(pw[1].a, 1);
-            if (lane == 0 && in && k > 0) {
-                zl = z[e - 1];
-                pl = pold[e - 1];
-                czl = CZ[e - 1];
+            ZT zl = __shfl_up(zw[1].b, 1), zr = __shfl_down(zw[1].a, 1);
+            double pl = __shfl_up(pw[1].b, 1), czl = __shfl_up(cz.b, 1), pr = __shfl_down(pw[1].a, 1);
+            if (le) {
+                zl = cur.ez;
+                pl = cur.ep;
+                czl = cur.ecz;
             }
-            if (lane == 63 && in && k + 2 < nz) {
-                zr = z[e + 2];
-                pr = pold[e + 2];
+            if (re) {
+                zr = cur.ez;
+                pr = cur.ep;
             }
-            auto row = [&](const Pair &c, const Pair &vu, const Pair &vd, double vl, double vr) {
+            auto row = [&](const auto &c, const auto &vu, const auto &vd, double vl, double vr) {
                 Pair y{d.a * c.a, d.b * c.b};
                 if (up) {
                     y.a -= cr.a * vu.a;
@@ -152,6 +207,7 @@ __device__ __forceinline__ void spmv_tiles(const double *__restrict__ z, const d
                 // stop flag is acted on after it (every workgroup alike)
                 const int done = st->done;
                 k_it = st->iters;
+                aprev = st->step.alpha;
                 const double rho_slot[2] = {st->rho[0], st->rho[1]};
                 const double rho = PR ? block_total(partials + SLOT_RZ * MAX_PARTIALS, n_rz, red)
                                       : total_finish(partials + SLOT_RZ * MAX_PARTIALS, n_rz, rz_pre, red);
@@ -166,12 +222,15 @@ __device__ __forceinline__ void spmv_tiles(const double *__restrict__ z, const d
             }
             if (in) {
                 double2 pn, qn;
-                pn.x = (k_it > 0) ? zw[1].a + beta * pw[1].a : zw[1].a;
-                pn.y = (k_it > 0) ? zw[1].b + beta * pw[1].b : zw[1].b;
+                pn.x = (k_it > 0) ? (double)zw[1].a + beta * pw[1].a : (double)zw[1].a;
+                pn.y = (k_it > 0) ? (double)zw[1].b + beta * pw[1].b : (double)zw[1].b;
                 qn.x = (k_it > 0) ? az.a + beta * ap.a : az.a;
                 qn.y = (k_it > 0) ? az.b + beta * ap.b : az.b;
                 *reinterpret_cast<double2 *>(pnew + e) = pn;
                 *reinterpret_cast<double2 *>(q + e) = qn;
+                if (k_it > 0)
+                    *reinterpret_cast<double2 *>(x + e) =
+                        make_double2(cur.x.a + aprev * pw[1].a, cur.x.b + aprev * pw[1].b);
                 acc += pn.x * qn.x;
                 acc += pn.y * qn.y;
             }
@@ -180,6 +239,7 @@ __device__ __forceinline__ void spmv_tiles(const double *__restrict__ z, const d
             pw[0] = pw[1];
             pw[1] = pw[2];
             crm = cr;
+            cur = nxt;
         }
     }
     const double s = block_sum(acc, red);
@@ -197,7 +257,7 @@ __device__ __forceinline__ void cheb_update_body(const double *__restrict__ d, d
 {
     __shared__ double red[8];
     if (st->done) return;
-    if (vb == 0 && threadIdx.x == 0) st->cur = st->iters;
+    if (vb == 0 && threadIdx.x == 0) st->step.cur = st->iters;
     double acc = 0.0;
     for (int b = vb; b < nr; b += vnb) {
         const int i = xcd_swizzle(b, nr);
@@ -255,19 +315,19 @@ __device__ __forceinline__ void init_body(const double *__restrict__ b, const do
 // to its resident workgroups): an SpMV tile, or a row.
 constexpr int BATCH_SPMV_RW = 16;   // rows per SpMV tile of a batch member
 
-inline int batch_spmv_tiles(int nr, int nz)
+inline int batch_spmv_tiles(int nr, int nz, int chunk)
 {
-    return ((nr + BATCH_SPMV_RW - 1) / BATCH_SPMV_RW) * ((nz + SPMV_CHUNK - 1) / SPMV_CHUNK);
+    return ((nr + BATCH_SPMV_RW - 1) / BATCH_SPMV_RW) * ((nz + chunk - 1) / chunk);
 }
 
-template <bool PR>
+template <typename T, bool PR, int CHUNK>
 __device__ __forceinline__ void b_spmv_item(const ProbDesc *__restrict__ d, int n, int g, int parity)
 {
     const int p = find_problem(d, n, g, RANGE_SP);
     const ProbDesc &P = d[p];
     const double *pold = parity ? P.p1 : P.p0;
     double *pnew = parity ? P.p0 : P.p1;
-    spmv_tiles<PR, BATCH_SPMV_RW>(P.z, pold, pnew, P.q, P.D, P.CR, P.CZ, P.nr, P.nz, P.state, P.partials, P.n_tr,
+    spmv_tiles<T, PR, BATCH_SPMV_RW, CHUNK>((const T *)P.z, pold, pnew, P.q, P.x, P.D, P.CR, P.CZ, P.nr, P.nz, P.state, P.partials, P.n_tr,
                                   g - P.sp_start, P.n_sp);
 }
 

@@ -23,8 +23,7 @@ struct Lines {
 // ---------------------------------------------------------------------------
 template <typename T, int BC, bool FUSED, int R2, int R>
 __device__ __forceinline__ bool
-strip_phase1(const double *__restrict__ rin, double *__restrict__ x, double *__restrict__ r,
-             const double *__restrict__ p, const double *__restrict__ q, PcgState *st,
+strip_phase1(const double *__restrict__ rin, double *__restrict__ r, const double *__restrict__ q, PcgState *st,
              double *__restrict__ partials, int n_pq, T *__restrict__ fprime, T *__restrict__ red_e,
              T *__restrict__ red_g, const typename vec2_of<T>::type *__restrict__ tw,
              const typename vec2_of<T>::type *__restrict__ pt, const Lines<T> &ln, int nr, int s, T *tile)
@@ -54,7 +53,7 @@ strip_phase1(const double *__restrict__ rin, double *__restrict__ x, double *__r
         }
     };
     if constexpr (!FUSED) load_lines();
-    if (!zfwd_w_body<T, BC, FUSED, R2>(rin, x, r, p, q, st, partials, n_pq, tw, pt, nr, i0 + wv, s,
+    if (!zfwd_w_body<T, BC, FUSED, R2>(rin, r, q, st, partials, n_pq, tw, pt, nr, i0 + wv, s,
                                         RowStore<T>{tile + wv * PITCH}))
         return false;
     if constexpr (FUSED) load_lines();
@@ -354,10 +353,11 @@ __device__ __forceinline__ void strip_solve2(T *__restrict__ red_x, const Lines<
 // ---------------------------------------------------------------------------
 template <typename T, int BC, int MODE, int R2, int R>
 __device__ __forceinline__ void
-strip_phase3(const T *__restrict__ fprime, const T *__restrict__ red_x, double *__restrict__ zout,
+strip_phase3(const T *__restrict__ fprime, const T *__restrict__ red_x, ZOut<T, MODE> *__restrict__ zout,
              const double *__restrict__ r, const PcgState *st, double *__restrict__ partials, bool pr,
              const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt,
-             const Lines<T> &ln, int nr, double *__restrict__ dinc, double tau, double rho2, int s, T *tile)
+             const Lines<T> &ln, int nr, double *__restrict__ dinc, double tau, double rho2, int s, T *tile,
+             const XFin &fin = XFin{})
 {
     using Gm = wfft::Geo<R2>;
     constexpr int N = Gm::N, PITCH = 2 * Gm::LB, n = R - 1, NT = 64 * R;
@@ -405,7 +405,10 @@ strip_phase3(const T *__restrict__ fprime, const T *__restrict__ red_x, double *
     const T cbm = s > 0 ? ln.cb[i0 - 1] : (T)0;
     // a stopped solve (every workgroup alike) returns here, its loads already
     // issued rather than waiting on the flag before them
-    if (MODE != 0 && st->done) return;
+    if (MODE != 0 && st->done) {
+        if (MODE == 1) x_finish(fin, st, (size_t)i0 * N, R * N, threadIdx.x, NT);
+        return;
+    }
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < NL; ++u) {

@@ -47,14 +47,13 @@ namespace {
 
 template <typename T, int BC, bool FUSED, int R2, int R>
 __global__ void __launch_bounds__(64 * R)
-k_strip_fwd(const double *__restrict__ rin, double *__restrict__ x, double *__restrict__ r,
-            const double *__restrict__ p, const double *__restrict__ q, PcgState *st, double *__restrict__ partials,
-            int n_pq, T *__restrict__ fprime, T *__restrict__ red_e, T *__restrict__ red_g,
+k_strip_fwd(const double *__restrict__ rin, double *__restrict__ r, const double *__restrict__ q, PcgState *st,
+            double *__restrict__ partials, int n_pq, T *__restrict__ fprime, T *__restrict__ red_e, T *__restrict__ red_g,
             const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt,
             Lines<T> ln, int nr)
 {
     extern __shared__ char smem_raw[];
-    strip_phase1<T, BC, FUSED, R2, R>(rin, x, r, p, q, st, partials, n_pq, fprime, red_e, red_g, tw, pt, ln, nr,
+    strip_phase1<T, BC, FUSED, R2, R>(rin, r, q, st, partials, n_pq, fprime, red_e, red_g, tw, pt, ln, nr,
                                       blockIdx.x, reinterpret_cast<T *>(smem_raw));
 }
 
@@ -80,14 +79,14 @@ k_strip_reduced(const T *__restrict__ red_e, const T *__restrict__ red_g, T *__r
 
 template <typename T, int BC, int MODE, int R2, int R>
 __global__ void __launch_bounds__(64 * R)
-k_strip_inv(const T *__restrict__ fprime, const T *__restrict__ red_x, double *__restrict__ zout,
+k_strip_inv(const T *__restrict__ fprime, const T *__restrict__ red_x, ZOut<T, MODE> *__restrict__ zout,
             const double *__restrict__ r, const PcgState *st, double *__restrict__ partials, bool pr,
             const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt,
-            Lines<T> ln, int nr, double *__restrict__ dinc, double tau, double rho2)
+            Lines<T> ln, int nr, double *__restrict__ dinc, double tau, double rho2, XFin fin)
 {
     extern __shared__ char smem_raw[];
     strip_phase3<T, BC, MODE, R2, R>(fprime, red_x, zout, r, st, partials, pr, tw, pt, ln, nr, dinc, tau, rho2,
-                                     blockIdx.x, reinterpret_cast<T *>(smem_raw));
+                                     blockIdx.x, reinterpret_cast<T *>(smem_raw), fin);
 }
 
 template <typename T>
@@ -152,12 +151,10 @@ void fwd_r(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     const dim3 grid(op.nr / R), block(64 * R);
     const size_t shm = (size_t)R * wfft::Geo<R2>::LB * sizeof(cx<T>);
     if (a.fused)
-        hipLaunchKernelGGL((k_strip_fwd<T, BC, true, R2, R>), grid, block, shm, s, nullptr, a.x, a.r, a.p, a.q,
-                           a.state, op.partials, a.n_pq, (T *)op.spec, rb.e, rb.g, tw_of<T>(op), pt_of<T>(op),
+        hipLaunchKernelGGL((k_strip_fwd<T, BC, true, R2, R>), grid, block, shm, s, nullptr, a.r, a.q, a.state, op.partials, a.n_pq, (T *)op.spec, rb.e, rb.g, tw_of<T>(op), pt_of<T>(op),
                            lines_of<T>(op), op.nr);
     else
-        hipLaunchKernelGGL((k_strip_fwd<T, BC, false, R2, R>), grid, block, shm, s, a.rin, nullptr, nullptr,
-                           nullptr, nullptr, a.state, op.partials, 0, (T *)op.spec, rb.e, rb.g, tw_of<T>(op),
+        hipLaunchKernelGGL((k_strip_fwd<T, BC, false, R2, R>), grid, block, shm, s, a.rin, nullptr, nullptr, a.state, op.partials, 0, (T *)op.spec, rb.e, rb.g, tw_of<T>(op),
                            pt_of<T>(op), lines_of<T>(op), op.nr);
     AXI_CHECK_HIP(hipGetLastError());
 }
@@ -173,8 +170,9 @@ void inv_r(const Operator &op, const ZinvArgs &a, hipStream_t s)
     const auto pt = pt_of<T>(op);
     const Lines<T> ln = lines_of<T>(op);
 #define AXI_SINV(MD, Z, RR, ST, PR, D)                                                                           \
-    hipLaunchKernelGGL((k_strip_inv<T, BC, MD, R2, R>), grid, block, shm, s, fp, rb.x, Z, RR, ST, op.partials,  \
-                       PR, tw, pt, ln, op.nr, D, a.tau, a.rho2)
+    hipLaunchKernelGGL((k_strip_inv<T, BC, MD, R2, R>), grid, block, shm, s, fp, rb.x, (ZOut<T, MD> *)(Z), RR,  \
+                       ST, op.partials,                                                                         \
+                       PR, tw, pt, ln, op.nr, D, a.tau, a.rho2, a.fin)
     switch (a.mode) {
     case 0: AXI_SINV(0, a.zout, nullptr, nullptr, false, nullptr); break;
     case 1: AXI_SINV(1, a.zout, a.r, a.state, a.pr, nullptr); break;

@@ -70,8 +70,7 @@ __device__ inline int wg_flag(const int *p)
 // stopped (or the step broke down): the whole workgroup then returns.
 template <typename T, int BC, bool FUSED, int R2, bool WG_STOP = false, typename Store>
 __device__ __forceinline__ bool
-zfwd_w_body(const double *__restrict__ rin, double *__restrict__ x, double *__restrict__ r,
-            const double *__restrict__ p, const double *__restrict__ q, PcgState *st,
+zfwd_w_body(const double *__restrict__ rin, double *__restrict__ r, const double *__restrict__ q, PcgState *st,
             double *__restrict__ partials, int n_pq,
             const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt,
             int nr, int row, int blk, const Store &store)
@@ -87,13 +86,11 @@ zfwd_w_body(const double *__restrict__ rin, double *__restrict__ x, double *__re
     const size_t base = (size_t)(valid ? row : nr - 1) * N + 2 * lane;
 
     // every global read first: the row (and the PCG vectors), the twiddles
-    double2 rv[R2], xv[R2], pv[R2], qv[R2];
+    double2 rv[R2], qv[R2];
 #pragma unroll
     for (int t = 0; t < R2; ++t) {
         if (FUSED) {
-            xv[t] = *reinterpret_cast<const double2 *>(x + base + 128 * t);
             rv[t] = *reinterpret_cast<const double2 *>(r + base + 128 * t);
-            pv[t] = *reinterpret_cast<const double2 *>(p + base + 128 * t);
             qv[t] = *reinterpret_cast<const double2 *>(q + base + 128 * t);
         } else {
             rv[t] = *reinterpret_cast<const double2 *>(rin + base + 128 * t);
@@ -128,7 +125,9 @@ zfwd_w_body(const double *__restrict__ rin, double *__restrict__ x, double *__re
             return false;
         }
         alpha = rho_slot[k_it & 1] / pq;
-        if (blk == 0 && threadIdx.x == 0) st->cur = k_it;
+        if (blk == 0 && threadIdx.x == 0) {
+            st->step = {alpha, k_it, 0};
+        }
     }
 
     // r update, Makhoul reordering into the slice (even k -> v[k/2], odd k -> v[N-1-(k-1)/2])
@@ -137,13 +136,9 @@ zfwd_w_body(const double *__restrict__ rin, double *__restrict__ x, double *__re
     for (int t = 0; t < R2; ++t) {
         double2 rn = rv[t];
         if (FUSED) {
-            double2 xn;
-            xn.x = xv[t].x + alpha * pv[t].x;
-            xn.y = xv[t].y + alpha * pv[t].y;
             rn.x = rv[t].x - alpha * qv[t].x;
             rn.y = rv[t].y - alpha * qv[t].y;
             if (valid) {
-                *reinterpret_cast<double2 *>(x + base + 128 * t) = xn;
                 *reinterpret_cast<double2 *>(r + base + 128 * t) = rn;
                 rr += rn.x * rn.x + rn.y * rn.y;
             }
@@ -215,6 +210,39 @@ zfwd_w_body(const double *__restrict__ rin, double *__restrict__ x, double *__re
     return true;
 }
 
+// x += alpha p over [base, base + n) (n even) by threads tid < nthr, when the
+// solve stopped in iteration fin.iter: forward ran (cur), with its step length.
+__device__ inline void x_finish(const XFin &fin, const PcgState *st, size_t base, int n, int tid, int nthr)
+{
+    const double alpha = st->step.alpha;
+    if (st->step.cur != fin.iter || alpha == 0.0) return;
+    for (int k = 2 * tid; k < n; k += 2 * nthr) {
+        const double2 p = *reinterpret_cast<const double2 *>(fin.p + base + k);
+        double2 *xp = reinterpret_cast<double2 *>(fin.x + base + k);
+        const double2 x = *xp;
+        *xp = make_double2(x.x + alpha * p.x, x.y + alpha * p.y);
+    }
+}
+
+// Element type of the inverse transforms' z: double for standalone applies,
+// the preconditioner's own type in the PCG modes.
+template <typename T, int MODE> struct ZOutOf { using type = double; };
+template <typename T> struct ZOutOf<T, 1> { using type = T; };
+template <typename T> struct ZOutOf<T, 2> { using type = T; };
+template <typename T, int MODE> using ZOut = typename ZOutOf<T, MODE>::type;
+
+__device__ inline double2 ld_pair(const double *p) { return *reinterpret_cast<const double2 *>(p); }
+__device__ inline double2 ld_pair(const float *p)
+{
+    const float2 v = *reinterpret_cast<const float2 *>(p);
+    return make_double2(v.x, v.y);
+}
+__device__ inline void st_pair(double *p, double2 v) { *reinterpret_cast<double2 *>(p) = v; }
+__device__ inline void st_pair(float *p, double2 v)
+{
+    *reinterpret_cast<float2 *>(p) = make_float2((float)v.x, (float)v.y);
+}
+
 // Inverse transform of row `row` by the calling wave: the spectral value of
 // index j comes from ld(j) (all of them are read before the wave's FFT uses
 // its LDS slice, so ld may read from that slice); z (or, in the Chebyshev
@@ -224,11 +252,11 @@ zfwd_w_body(const double *__restrict__ rin, double *__restrict__ x, double *__re
 // pairs the body would load, t < R2), already loaded by the caller.
 template <typename T, int BC, int MODE, int R2, typename Load>
 __device__ __forceinline__ void
-zinv_w_body(const Load &ld, double *__restrict__ zout, const double *__restrict__ r,
+zinv_w_body(const Load &ld, ZOut<T, MODE> *__restrict__ zout, const double *__restrict__ r,
             const PcgState *st, double *__restrict__ partials, bool pr,
             const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt,
             int nr, double *__restrict__ dinc, double tau, double rho2, int row, int blk,
-            const double2 *rpre = nullptr)
+            const double2 *rpre = nullptr, const XFin &fin = XFin{})
 {
     constexpr bool PCGM = (MODE == 1 || MODE == 2);
     constexpr bool CHEB = (MODE == 3 || MODE == 4);
@@ -268,11 +296,14 @@ zinv_w_body(const Load &ld, double *__restrict__ zout, const double *__restrict_
     for (int t = 0; t < R2; ++t) {
         if (PCGM) {
             rv[t] = rpre ? rpre[t] : *reinterpret_cast<const double2 *>(r + base + 128 * t);
-            if (pr) zo[t] = *reinterpret_cast<const double2 *>(zout + base + 128 * t);
+            if (pr) zo[t] = ld_pair(zout + base + 128 * t);
         }
         if (MODE == 3) dv[t] = *reinterpret_cast<const double2 *>(dinc + base + 128 * t);
     }
-    if (MODE != 0 && st->done) return;
+    if (MODE != 0 && st->done) {
+        if (MODE == 1 && valid) x_finish(fin, st, (size_t)row * N, N, lane, 64);
+        return;
+    }
     double c1 = 0.0, c2 = 0.0;
     if (CHEB) {
         const double alpha = cheb_alpha(st->iters + 1, rho2);
@@ -325,7 +356,6 @@ zinv_w_body(const Load &ld, double *__restrict__ zout, const double *__restrict_
         const T yo = fbuf[wfft::fslot(N - 1 - sv)];
         zv.y = (double)((BC == DIR) ? -yo : yo);
         if (!valid) continue;
-        double *dst = (CHEB ? dinc : zout) + base + 128 * t;
         if (PCGM) {
             if (pr) rzo += rv[t].x * zo[t].x + rv[t].y * zo[t].y;
             rz += rv[t].x * zv.x + rv[t].y * zv.y;
@@ -334,9 +364,9 @@ zinv_w_body(const Load &ld, double *__restrict__ zout, const double *__restrict_
             double2 d;
             d.x = (MODE == 4) ? c2 * zv.x : c1 * dv[t].x + c2 * zv.x;
             d.y = (MODE == 4) ? c2 * zv.y : c1 * dv[t].y + c2 * zv.y;
-            *reinterpret_cast<double2 *>(dst) = d;
+            *reinterpret_cast<double2 *>(dinc + base + 128 * t) = d;
         } else {
-            *reinterpret_cast<double2 *>(dst) = zv;
+            st_pair(zout + base + 128 * t, zv);
         }
     }
     if (PCGM) {
@@ -364,7 +394,7 @@ __device__ inline void publish(HostMirror *m, unsigned seq, double rr, double bb
 // round of the ||r||^2 partials, issued before the launch stages its own
 // data so that the two latencies overlap.
 struct GatePre {
-    TotalLoads rr;
+    TotalLoads<8> rr;
     int done, cur, maxit;
     double tol2;
 };
@@ -373,7 +403,7 @@ __device__ inline void gate_issue(const PcgState *st, const double *__restrict__
                                   GatePre &p)
 {
     p.done = st->done;
-    p.cur = st->cur;
+    p.cur = st->step.cur;
     p.maxit = st->maxit;
     p.tol2 = st->tol2;
     total_issue(partials + SLOT_RR * MAX_PARTIALS, g.n_rr, p.rr);
@@ -418,7 +448,7 @@ __device__ inline int tridiag_gate(PcgState *st, const double *__restrict__ part
         st->bb = bb;
         st->tol2 = tol2;
         st->iters = 0;
-        st->cur = 0;
+        st->step = {0.0, 0, 0};
         st->maxit = g.maxit;
         st->flags = g.flags;
         st->done = status;

@@ -26,7 +26,7 @@ __device__ inline const typename vec2_of<T>::type *stage_twiddles(const typename
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int k = base + (int)threadIdx.x + j * (int)blockDim.x;
-            if (k < N) v[j] = tw[k];
+            v[j] = tw[k < N ? k : 0];
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -45,8 +45,7 @@ __device__ inline const typename vec2_of<T>::type *stage_twiddles(const typename
 // issued while the first row is reordered into LDS.
 // ---------------------------------------------------------------------------
 template <typename T, int BC, bool FUSED, bool TWLDS, int ROWS, bool WG_STOP = false>
-__device__ __forceinline__ void zfwd_body(const double *__restrict__ rin, double *__restrict__ x,
-                                          double *__restrict__ r, const double *__restrict__ p,
+__device__ __forceinline__ void zfwd_body(const double *__restrict__ rin, double *__restrict__ r,
                                           const double *__restrict__ q, PcgState *st,
                                           double *__restrict__ partials, int n_pq, T *__restrict__ spec,
                                           const typename vec2_of<T>::type *__restrict__ tw,
@@ -60,14 +59,26 @@ __device__ __forceinline__ void zfwd_body(const double *__restrict__ rin, double
     V2 *twl = reinterpret_cast<V2 *>(b + N);
     __shared__ double red[RED_SLOTS];
 
-    if constexpr (WG_STOP) {
-        if (st && wg_flag(&st->done)) return;
-    } else {
+    const int i0 = xcd_swizzle(vb, nr / ROWS) * ROWS;
+    // PCG step: the state fields and the first round of the p.q partials are
+    // read with the row and the twiddles, so that one trip to memory serves
+    // them all; the stop flag is acted on after it.  (The plain transform of
+    // FP64 rows of 2048 took 36.5 us that way, 33.4 with the flag first.)
+    int done = 0, k_it = 0;
+    if constexpr (FUSED && !WG_STOP) done = st->done;
+    if constexpr (!FUSED && !WG_STOP) {
         if (st && st->done) return;
     }
-    const int i0 = xcd_swizzle(vb, nr / ROWS) * ROWS;
+    double rho_slot[2] = {0.0, 0.0};
+    TotalLoads<2> pq_pre;
+    if (FUSED) {
+        k_it = st->iters;
+        rho_slot[0] = st->rho[0];
+        rho_slot[1] = st->rho[1];
+        total_issue(partials + SLOT_PQ * MAX_PARTIALS, n_pq, pq_pre);
+    }
     constexpr int KPT = 8;   // elements per thread (fft_threads gives N <= 8 blockDim.x)
-    double xv[KPT], rv0[KPT], pv[KPT], qv[KPT];
+    double rv0[KPT], qv[KPT];
     auto load = [&](int i) {
         const size_t row = (size_t)i * N;
 #pragma unroll
@@ -75,9 +86,7 @@ __device__ __forceinline__ void zfwd_body(const double *__restrict__ rin, double
             const int k = threadIdx.x + j * blockDim.x;
             if (k < N) {
                 if (FUSED) {
-                    xv[j] = x[row + k];
                     rv0[j] = r[row + k];
-                    pv[j] = p[row + k];
                     qv[j] = q[row + k];
                 } else {
                     rv0[j] = rin[row + k];
@@ -85,19 +94,24 @@ __device__ __forceinline__ void zfwd_body(const double *__restrict__ rin, double
             }
         }
     };
-    // issue the first row's loads before the p.q reduction so the latencies overlap
     load(i0);
     const V2 *twp = TWLDS ? stage_twiddles<T>(tw, twl, N) : tw;
+    if constexpr (WG_STOP) {
+        if (st && wg_flag(&st->done)) return;
+    } else {
+        if (done) return;
+    }
     double alpha = 0.0;
     if (FUSED) {
-        const double pq = block_total(partials + SLOT_PQ * MAX_PARTIALS, n_pq, red);
-        const int k_it = st->iters;
+        const double pq = total_finish(partials + SLOT_PQ * MAX_PARTIALS, n_pq, pq_pre, red);
         if (!(pq > 0.0) || !(pq < 1e308)) {
             if (vb == 0 && threadIdx.x == 0) st->done = ST_BREAK;
             return;
         }
-        alpha = st->rho[k_it & 1] / pq;
-        if (vb == 0 && threadIdx.x == 0) st->cur = k_it;
+        alpha = rho_slot[k_it & 1] / pq;
+        if (vb == 0 && threadIdx.x == 0) {
+            st->step = {alpha, k_it, 0};
+        }
     }
 
     double rr = 0.0;
@@ -116,7 +130,6 @@ __device__ __forceinline__ void zfwd_body(const double *__restrict__ rin, double
             double rv;
             if (FUSED) {
                 const size_t c = row + k;
-                x[c] = xv[j] + alpha * pv[j];
                 rv = rv0[j] - alpha * qv[j];
                 r[c] = rv;
                 rr += rv * rv;
@@ -179,17 +192,25 @@ __device__ __forceinline__ void zfwd_body(const double *__restrict__ rin, double
 // ---------------------------------------------------------------------------
 
 template <typename T, int BC, int MODE, bool TWLDS, int ROWS>
-__device__ __forceinline__ void zinv_body(const T *__restrict__ spec, double *__restrict__ zout,
+__device__ __forceinline__ void zinv_body(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout,
                                           const double *__restrict__ r, const PcgState *st,
                                           double *__restrict__ partials, bool pr,
                                           const typename vec2_of<T>::type *__restrict__ tw,
                                           const typename vec2_of<T>::type *__restrict__ pt, int nr, int N, int vb,
-                                          double *__restrict__ dinc = nullptr, double tau = 0.0, double rho2 = 0.0)
+                                          double *__restrict__ dinc = nullptr, double tau = 0.0, double rho2 = 0.0,
+                                          const XFin &fin = XFin{})
 {
     constexpr bool PCGM = (MODE == 1 || MODE == 2);
     constexpr bool CHEB = (MODE == 3 || MODE == 4);
     using V2 = typename vec2_of<T>::type;
-    if (MODE != 0 && st->done) return;
+    const int i0 = xcd_swizzle(vb, nr / ROWS) * ROWS;
+    // read with the row and the twiddles and acted on after them (every
+    // workgroup alike), so that one trip to memory serves all
+    const int done = MODE != 0 ? st->done : 0;
+    auto stopped = [&]() {
+        if (done && MODE == 1) x_finish(fin, st, (size_t)i0 * N, ROWS * N, threadIdx.x, blockDim.x);
+        return done != 0;
+    };
     extern __shared__ char smem_raw[];
     cx<T> *a = reinterpret_cast<cx<T> *>(smem_raw);
     cx<T> *b = a + N;
@@ -197,7 +218,6 @@ __device__ __forceinline__ void zinv_body(const T *__restrict__ spec, double *__
     __shared__ double red[RED_SLOTS];
     const V2 *twp = TWLDS ? stage_twiddles<T>(tw, twl, N) : tw;
 
-    const int i0 = xcd_swizzle(vb, nr / ROWS) * ROWS;
     const T isc = (T)sqrt(0.5 * N);      // 1 / sqrt(2/N)
     const T sq2 = (T)1.41421356237309504880;
     constexpr int KPT = 8;   // fft_threads gives N <= 8 blockDim.x
@@ -264,7 +284,7 @@ __device__ __forceinline__ void zinv_body(const T *__restrict__ spec, double *__
                 if (MODE == 4) dinc[rowt + k] = c2 * zv;
                 else dinc[rowt + k] = c1 * dinc[rowt + k] + c2 * zv;
             } else {
-                zout[rowt + k] = zv;
+                zout[rowt + k] = (ZOut<T, MODE>)zv;
             }
         }
     };
@@ -282,6 +302,7 @@ __device__ __forceinline__ void zinv_body(const T *__restrict__ spec, double *__
             load_r(0);
             load_r(1);
         }
+        if (stopped()) return;
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < KPT; ++j) {
@@ -311,6 +332,7 @@ __device__ __forceinline__ void zinv_body(const T *__restrict__ spec, double *__
             }
         }
         if (PCGM) load_r(0);
+        if (stopped()) return;
         __syncthreads();
         const cx<T> *res = fft_stockham<T>(a, b, N, twp);
         store(res, 0, 0);
@@ -559,71 +581,76 @@ template <> __device__ inline const double2 *pd_pt<double>(const ProbDesc &P) { 
 // returns once the member has stopped.  The inverse transforms' modes 3 and 4
 // form the Chebyshev increment in the member's p0 buffer with its tau, rho2.
 template <typename T, bool FUSED, bool TWLDS, bool WG_STOP, bool GATE = false>
-__device__ __forceinline__ void b_zfwd_item(const ProbDesc *__restrict__ d, int n, int g, int parity)
+__device__ __forceinline__ void b_zfwd_item(const ProbDesc *__restrict__ d, int n, int g)
 {
     const int p = find_problem(d, n, g, RANGE_TR);
     const ProbDesc &P = d[p];
-    const double *pnew = parity ? P.p0 : P.p1;   // written by this iteration's SpMV
     const int vb = g - P.tr_start;
     // the start-up transform runs before the r-solve launch resets the state,
     // so only the in-loop transforms may read the stop flag
     PcgState *st = (FUSED || GATE) ? P.state : nullptr;
     if (P.bc_z == DIR)
-        zfwd_body<T, DIR, FUSED, TWLDS, 1, WG_STOP>(P.r, P.x, P.r, pnew, P.q, st, P.partials, P.n_sp, (T *)P.spec,
-                                        pd_tw<T>(P), pd_pt<T>(P), P.nr, P.nz, vb);
+        zfwd_body<T, DIR, FUSED, TWLDS, 1, WG_STOP>(P.r, P.r, P.q, st, P.partials, P.n_sp, (T *)P.spec, pd_tw<T>(P),
+                                                    pd_pt<T>(P), P.nr, P.nz, vb);
     else
-        zfwd_body<T, AXIPCG_Z_NEUMANN, FUSED, TWLDS, 1, WG_STOP>(P.r, P.x, P.r, pnew, P.q, st, P.partials, P.n_sp,
-                                                     (T *)P.spec, pd_tw<T>(P), pd_pt<T>(P), P.nr, P.nz, vb);
+        zfwd_body<T, AXIPCG_Z_NEUMANN, FUSED, TWLDS, 1, WG_STOP>(P.r, P.r, P.q, st, P.partials, P.n_sp, (T *)P.spec,
+                                                                 pd_tw<T>(P), pd_pt<T>(P), P.nr, P.nz, vb);
 }
 
+// The last x update of a member that stopped in iteration `iter` (mode 1).
+__device__ inline XFin pd_fin(const ProbDesc &P, int iter) { return {P.x, (iter & 1) ? P.p0 : P.p1, iter}; }
+
 template <typename T, int MODE, bool TWLDS>
-__device__ __forceinline__ void b_zinv_item(const ProbDesc *__restrict__ d, int n, int g, bool pr)
+__device__ __forceinline__ void b_zinv_item(const ProbDesc *__restrict__ d, int n, int g, bool pr, int iter)
 {
     const int p = find_problem(d, n, g, RANGE_TR);
     const ProbDesc &P = d[p];
     const int vb = g - P.tr_start;
+    const XFin fin = pd_fin(P, iter);
     if (P.bc_z == DIR)
-        zinv_body<T, DIR, MODE, TWLDS, 1>((const T *)P.spec, P.z, P.r, P.state, P.partials, pr, pd_tw<T>(P),
-                                       pd_pt<T>(P), P.nr, P.nz, vb, P.p0, P.tau, P.rho2);
+        zinv_body<T, DIR, MODE, TWLDS, 1>((const T *)P.spec, (ZOut<T, MODE> *)P.z, P.r, P.state, P.partials, pr,
+                                          pd_tw<T>(P), pd_pt<T>(P), P.nr, P.nz, vb, P.p0, P.tau, P.rho2, fin);
     else
-        zinv_body<T, AXIPCG_Z_NEUMANN, MODE, TWLDS, 1>((const T *)P.spec, P.z, P.r, P.state, P.partials, pr,
-                                                    pd_tw<T>(P), pd_pt<T>(P), P.nr, P.nz, vb, P.p0, P.tau, P.rho2);
+        zinv_body<T, AXIPCG_Z_NEUMANN, MODE, TWLDS, 1>((const T *)P.spec, (ZOut<T, MODE> *)P.z, P.r, P.state,
+                                                       P.partials, pr, pd_tw<T>(P), pd_pt<T>(P), P.nr, P.nz, vb, P.p0,
+                                                       P.tau, P.rho2, fin);
 }
 
 template <typename T, bool FUSED, int R2, bool WG_STOP, bool GATE = false>
-__device__ __forceinline__ void b_zfwd_w_item(const ProbDesc *__restrict__ d, int n, int g, int parity)
+__device__ __forceinline__ void b_zfwd_w_item(const ProbDesc *__restrict__ d, int n, int g)
 {
     const int p = find_problem(d, n, g, RANGE_TR);
     const ProbDesc &P = d[p];
-    const double *pnew = parity ? P.p0 : P.p1;
     const int vb = g - P.tr_start;
     PcgState *st = (FUSED || GATE) ? P.state : nullptr;   // as in b_zfwd_item
     constexpr int WR = wave_rows<T, R2>();
     const int row = vb * WR + (threadIdx.x >> 6);
     RowStore<T> out{(T *)P.spec + (size_t)(row < P.nr ? row : 0) * wfft::Geo<R2>::N};
     if (P.bc_z == DIR)
-        zfwd_w_body<T, DIR, FUSED, R2, WG_STOP>(P.r, P.x, P.r, pnew, P.q, st, P.partials, P.n_sp, pd_tw<T>(P), pd_pt<T>(P),
-                                       P.nr, row, vb, out);
+        zfwd_w_body<T, DIR, FUSED, R2, WG_STOP>(P.r, P.r, P.q, st, P.partials, P.n_sp, pd_tw<T>(P), pd_pt<T>(P), P.nr,
+                                                row, vb, out);
     else
-        zfwd_w_body<T, AXIPCG_Z_NEUMANN, FUSED, R2, WG_STOP>(P.r, P.x, P.r, pnew, P.q, st, P.partials, P.n_sp, pd_tw<T>(P),
-                                                    pd_pt<T>(P), P.nr, row, vb, out);
+        zfwd_w_body<T, AXIPCG_Z_NEUMANN, FUSED, R2, WG_STOP>(P.r, P.r, P.q, st, P.partials, P.n_sp, pd_tw<T>(P),
+                                                             pd_pt<T>(P), P.nr, row, vb, out);
 }
 
 template <typename T, int MODE, int R2>
-__device__ __forceinline__ void b_zinv_w_item(const ProbDesc *__restrict__ d, int n, int g, bool pr)
+__device__ __forceinline__ void b_zinv_w_item(const ProbDesc *__restrict__ d, int n, int g, bool pr, int iter)
 {
     const int p = find_problem(d, n, g, RANGE_TR);
     const ProbDesc &P = d[p];
     const int vb = g - P.tr_start;
     constexpr int WR = wave_rows<T, R2>();
     const int row = vb * WR + (threadIdx.x >> 6);
+    const XFin fin = pd_fin(P, iter);
     RowLoad<T> in{(const T *)P.spec + (size_t)(row < P.nr ? row : P.nr - 1) * wfft::Geo<R2>::N};
     if (P.bc_z == DIR)
-        zinv_w_body<T, DIR, MODE, R2>(in, P.z, P.r, P.state, P.partials, pr, pd_tw<T>(P), pd_pt<T>(P), P.nr, P.p0,
-                                      P.tau, P.rho2, row, vb);
+        zinv_w_body<T, DIR, MODE, R2>(in, (ZOut<T, MODE> *)P.z, P.r, P.state, P.partials, pr, pd_tw<T>(P),
+                                      pd_pt<T>(P), P.nr, P.p0, P.tau, P.rho2, row, vb, nullptr, fin);
     else
-        zinv_w_body<T, AXIPCG_Z_NEUMANN, MODE, R2>(in, P.z, P.r, P.state, P.partials, pr, pd_tw<T>(P), pd_pt<T>(P),
-                                                   P.nr, P.p0, P.tau, P.rho2, row, vb);
+        zinv_w_body<T, AXIPCG_Z_NEUMANN, MODE, R2>(in, (ZOut<T, MODE> *)P.z, P.r, P.state, P.partials, pr,
+                                                   pd_tw<T>(P), pd_pt<T>(P), P.nr, P.p0, P.tau, P.rho2, row, vb,
+                                                   nullptr, fin);
 }
 
 template <typename T>
