@@ -3,15 +3,15 @@
 // r-tridiagonal solver, for one operator and for a batch, with their plans
 // (rows per workgroup, LDS, twiddle placement).  The device bodies are in
 // xform.h and wxform.h.
+#include "bxform.h"
 #include "xform.h"
 
 namespace axipcg {
 
 namespace {
 
-// (512 threads for N = 4096, 256 or fewer below)
 template <typename T, int BC, bool FUSED, bool TWLDS, int ROWS>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(256)
 k_zfwd(const double *__restrict__ rin, double *__restrict__ r, const double *__restrict__ q, PcgState *st,
        double *__restrict__ partials, int n_pq,
        T *__restrict__ spec, const typename vec2_of<T>::type *__restrict__ tw,
@@ -21,7 +21,7 @@ k_zfwd(const double *__restrict__ rin, double *__restrict__ r, const double *__r
 }
 
 template <typename T, int BC, int MODE, bool TWLDS, int ROWS>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(256)
 k_zinv(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout, const double *__restrict__ r,
        const PcgState *st, double *__restrict__ partials, bool pr,
        const typename vec2_of<T>::type *__restrict__ tw,
@@ -29,6 +29,25 @@ k_zinv(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout, const doubl
        double rho2, XFin fin)
 {
     zinv_body<T, BC, MODE, TWLDS, ROWS>(spec, zout, r, st, partials, pr, tw, pt, nr, N, blockIdx.x, dinc, tau, rho2, fin);
+}
+
+template <typename T, int BC, bool FUSED, int N, int ROWS>
+__global__ void __launch_bounds__(N / 8)
+k_zfwd8(const double *__restrict__ rin, double *__restrict__ r, const double *__restrict__ q, PcgState *st,
+        double *__restrict__ partials, int n_pq, T *__restrict__ spec,
+        const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt, int nr)
+{
+    zfwd8_body<T, BC, FUSED, N, ROWS>(rin, r, q, st, partials, n_pq, spec, tw, pt, nr, blockIdx.x);
+}
+
+template <typename T, int BC, int MODE, int N, int ROWS>
+__global__ void __launch_bounds__(N / 8)
+k_zinv8(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout, const double *__restrict__ r,
+        const PcgState *st, double *__restrict__ partials, bool pr,
+        const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt, int nr,
+        double *__restrict__ dinc, double tau, double rho2, XFin fin)
+{
+    zinv8_body<T, BC, MODE, N, ROWS>(spec, zout, r, st, partials, pr, tw, pt, nr, blockIdx.x, dinc, tau, rho2, fin);
 }
 
 template <typename T, int BC, bool FUSED, int R2>
@@ -135,15 +154,17 @@ bool twiddles_in_lds(int N) { return 3 * (size_t)N * sizeof(cx<T>) <= 65536; }
 template <typename T>
 size_t transform_lds(int N) { return (twiddles_in_lds<T>(N) ? 3 : 2) * (size_t)N * sizeof(cx<T>); }
 
-// Rows per transform workgroup: two (pipelined) for the FP64 transforms, and
-// for the FP32 ones of rows of 4096 points, when that still leaves at least
-// 256 workgroups, else one.  (Measured at 1024^2: two rows take the FP64
-// forward transform from 28 to 25 us but slow the FP32 ones, whose FFT is too
-// short to hide a second row's loads behind while the grid loses half its
-// workgroups; at 4096^2 the FP32 apply goes from 528 to 503 us with two.)
+// Rows per transform workgroup of the block-wide forms: two, which share one
+// complex FFT, when that still leaves at least 256 workgroups, else one; the
+// FP32 Stockham form (rows of up to 128 points) takes one, its FFT being too
+// short to hide a second row's loads behind.  Rows of 2048 and more (bxform.h)
+// pair any nr, the others (xform.h) an even one.
+inline bool block8(int nz) { return nz >= 2048; }
 inline int transform_rows(int nr, int nz, int prec)
 {
-    return ((prec == AXIPCG_PREC_FP64 || nz >= 4096) && nr % 2 == 0 && nr >= 512) ? 2 : 1;
+    if (nr < 512) return 1;
+    if (block8(nz)) return 2;
+    return (prec == AXIPCG_PREC_FP64 && nr % 2 == 0) ? 2 : 1;
 }
 
 // Dynamic LDS above the default 64 KiB (FP64 rows of 4096) needs the
@@ -202,6 +223,24 @@ void zfwd_wave(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     AXI_CHECK_HIP(hipGetLastError());
 }
 
+template <typename T, int BC, int N, int ROWS>
+void zfwd8_t(const Operator &op, const ZfwdArgs &a, hipStream_t s)
+{
+    using F = BlockFft<T, N>;
+    const auto tb = tables<T>(op);
+    const dim3 grid((op.nr + ROWS - 1) / ROWS), block(F::NT);
+    static bool lds_set[2] = {false, false};
+    allow_transform_lds(reinterpret_cast<const void *>(&k_zfwd8<T, BC, true, N, ROWS>), F::LDS, lds_set[0]);
+    allow_transform_lds(reinterpret_cast<const void *>(&k_zfwd8<T, BC, false, N, ROWS>), F::LDS, lds_set[1]);
+    if (a.fused)
+        hipLaunchKernelGGL((k_zfwd8<T, BC, true, N, ROWS>), grid, block, F::LDS, s, nullptr, a.r, a.q, a.state,
+                           op.partials, a.n_pq, (T *)op.spec, tb.tw, tb.pt, op.nr);
+    else
+        hipLaunchKernelGGL((k_zfwd8<T, BC, false, N, ROWS>), grid, block, F::LDS, s, a.rin, nullptr, nullptr, a.state,
+                           op.partials, 0, (T *)op.spec, tb.tw, tb.pt, op.nr);
+    AXI_CHECK_HIP(hipGetLastError());
+}
+
 template <typename T, int BC>
 void zfwd_t(const Operator &op, const ZfwdArgs &a, hipStream_t s)
 {
@@ -214,14 +253,18 @@ void zfwd_t(const Operator &op, const ZfwdArgs &a, hipStream_t s)
         break;
     default: break;
     }
-    const bool twl = twiddles_in_lds<T>(op.nz);
-    if (transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32) == 2) {
-        if (twl) zfwd_ttr<T, BC, true, 2>(op, a, s);
-        else zfwd_ttr<T, BC, false, 2>(op, a, s);
-    } else {
-        if (twl) zfwd_ttr<T, BC, true, 1>(op, a, s);
-        else zfwd_ttr<T, BC, false, 1>(op, a, s);
+    const int rows = transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32);
+    if (block8(op.nz)) {
+        if constexpr (sizeof(T) == 8) {
+            if (op.nz == 2048) return rows == 2 ? zfwd8_t<T, BC, 2048, 2>(op, a, s) : zfwd8_t<T, BC, 2048, 1>(op, a, s);
+        }
+        return rows == 2 ? zfwd8_t<T, BC, 4096, 2>(op, a, s) : zfwd8_t<T, BC, 4096, 1>(op, a, s);
     }
+    // rows of up to 128 points, whose twiddles fit LDS
+    if constexpr (sizeof(T) == 8) {
+        if (rows == 2) return zfwd_ttr<T, BC, true, 2>(op, a, s);
+    }
+    zfwd_ttr<T, BC, true, 1>(op, a, s);
 }
 
 template <typename T, int BC, bool TWL, int ROWS>
@@ -296,6 +339,30 @@ void zinv_wave(const Operator &op, const ZinvArgs &a, hipStream_t s)
     AXI_CHECK_HIP(hipGetLastError());
 }
 
+template <typename T, int BC, int N, int ROWS>
+void zinv8_t(const Operator &op, const ZinvArgs &a, hipStream_t s)
+{
+    using F = BlockFft<T, N>;
+    const auto tb = tables<T>(op);
+    const dim3 grid((op.nr + ROWS - 1) / ROWS), block(F::NT);
+#define AXI_ZINV8(MD, Z, RR, ST, PR, D)                                                                             \
+    do {                                                                                                           \
+        static bool lds_set = false;                                                                               \
+        allow_transform_lds(reinterpret_cast<const void *>(&k_zinv8<T, BC, MD, N, ROWS>), F::LDS, lds_set);         \
+        hipLaunchKernelGGL((k_zinv8<T, BC, MD, N, ROWS>), grid, block, F::LDS, s, (const T *)op.spec,               \
+                           (ZOut<T, MD> *)(Z), RR, ST, op.partials, PR, tb.tw, tb.pt, op.nr, D, a.tau, a.rho2, a.fin); \
+    } while (0)
+    switch (a.mode) {
+    case 0: AXI_ZINV8(0, a.zout, nullptr, nullptr, false, nullptr); break;
+    case 1: AXI_ZINV8(1, a.zout, a.r, a.state, a.pr, nullptr); break;
+    case 2: AXI_ZINV8(2, a.zout, a.r, a.state, false, nullptr); break;
+    case 3: AXI_ZINV8(3, nullptr, nullptr, a.state, false, a.d); break;
+    default: AXI_ZINV8(4, nullptr, nullptr, a.state, false, a.d); break;
+    }
+#undef AXI_ZINV8
+    AXI_CHECK_HIP(hipGetLastError());
+}
+
 template <typename T, int BC>
 void zinv_t(const Operator &op, const ZinvArgs &a, hipStream_t s)
 {
@@ -308,14 +375,17 @@ void zinv_t(const Operator &op, const ZinvArgs &a, hipStream_t s)
         break;
     default: break;
     }
-    const bool twl = twiddles_in_lds<T>(op.nz);
-    if (transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32) == 2) {
-        if (twl) zinv_ttr<T, BC, true, 2>(op, a, s);
-        else zinv_ttr<T, BC, false, 2>(op, a, s);
-    } else {
-        if (twl) zinv_ttr<T, BC, true, 1>(op, a, s);
-        else zinv_ttr<T, BC, false, 1>(op, a, s);
+    const int rows = transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32);
+    if (block8(op.nz)) {
+        if constexpr (sizeof(T) == 8) {
+            if (op.nz == 2048) return rows == 2 ? zinv8_t<T, BC, 2048, 2>(op, a, s) : zinv8_t<T, BC, 2048, 1>(op, a, s);
+        }
+        return rows == 2 ? zinv8_t<T, BC, 4096, 2>(op, a, s) : zinv8_t<T, BC, 4096, 1>(op, a, s);
     }
+    if constexpr (sizeof(T) == 8) {
+        if (rows == 2) return zinv_ttr<T, BC, true, 2>(op, a, s);
+    }
+    zinv_ttr<T, BC, true, 1>(op, a, s);
 }
 
 // LDS of an r-solve workgroup (its [M][N_r] tile, padded): up to 136 KiB, so
@@ -396,7 +466,8 @@ int transform_blocks(const Operator &op, int prec)
     if (strip_usable(op, prec, strip_solve_rows(op, prec))) return op.nr / strip_solve_rows(op, prec);
     const int wr = (prec == AXIPCG_PREC_FP32) ? wave_plan_rows<float>(op.nz) : wave_plan_rows<double>(op.nz);
     if (wr > 0) return (op.nr + wr - 1) / wr;
-    return op.nr / transform_rows(op.nr, op.nz, prec);
+    const int rows = transform_rows(op.nr, op.nz, prec);
+    return (op.nr + rows - 1) / rows;
 }
 
 // ---- batched launchers -------------------------------------------------------
