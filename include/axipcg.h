@@ -143,13 +143,14 @@ int axipcg_precond_apply(axipcg_op_t op, const double *r, double *z, int prec, v
  * the elimination of its interior rows in terms of the strips' last rows, (2)
  * per z-mode the tridiagonal system of those last rows (nr/R unknowns), (3)
  * the strips' interior rows and the inverse transform.  It applies when nz is
- * 256..2048 (FP32) or 256..1024 (FP64) and nr is a multiple of R with
- * nr/R <= 1024; otherwise, or when set_strips disables it for the handle, the
+ * 256..2048 (FP32) or 256..1024 (FP64), ceil(nr/R) <= 1024 strips in all (the
+ * last one is completed by uncoupled rows when R does not divide nr);
+ * otherwise, or when set_strips disables it for the handle, the
  * per-mode r-solve of eq. (39) over the whole line runs instead.  Both
  * compute the same B^{-1} r up to rounding.  set_strips takes 0 (off), 1 (on,
  * the default height R = 4), 4 or 8; other values return AXIPCG_EINVAL.
- * Standalone FP32 applies of rows of length 2048 use strips of 8 rows
- * (faster there), and the solves' FP32 launches at that length use strips of
+ * Standalone FP32 applies of rows of length 2048 use strips of 8 rows where 8
+ * divides nr (faster there), and the solves' FP32 launches at that length use strips of
  * 4 whatever the height (their in-loop kernels need the registers of 4-wave
  * workgroups); strips_info reports the solves' strips.
  * strips_info reports whether the strip form is used for `prec` and its

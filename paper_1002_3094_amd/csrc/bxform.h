@@ -96,6 +96,62 @@ struct BlockFft {
     }
 };
 
+// Has the value computed here: the compiler's code sinking moves LDS reads whose
+// results are first used in a later block down past the workgroup barriers in
+// between, where others already overwrite the buffer.
+template <typename T>
+__device__ __forceinline__ void in_register(T &v) { asm volatile("" : "+v"(v)); }
+
+// Spectra of one row (ROWS 1) or of two, both real, through one complex FFT
+// (the second row in the imaginary parts, zero unless `two`): v0, v1 hold the
+// thread's pairs (2 (t + j NT), + 1), s0, s1 receive modes t + e NT.  The
+// buffer is free on entry and may still be read by others on exit, this
+// thread's reads done.
+template <typename T, int BC, int N, int ROWS>
+__device__ __forceinline__ void pair_spectra(const double2 (&v0)[4], const double2 (&v1)[4], bool two, cx<T> *buf,
+                                             const typename vec2_of<T>::type *__restrict__ tw,
+                                             const typename vec2_of<T>::type *__restrict__ pt, T (&s0)[8], T (&s1)[8])
+{
+    using F = BlockFft<T, N>;
+    constexpr int NT = F::NT;
+    const int t = threadIdx.x;
+    // even k -> v[k/2], odd k -> v[N-1-(k-1)/2] (sine: y_k = (-1)^k x_k)
+    const T sg = (BC == DIR) ? (T)-1 : (T)1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int n = t + j * NT;
+        buf[F::at(n)] = {(T)v0[j].x, two ? (T)v1[j].x : (T)0};
+        buf[F::at(N - 1 - n)] = {sg * (T)v0[j].y, two ? sg * (T)v1[j].y : (T)0};
+    }
+    __syncthreads();
+    cx<T> v[8];
+    F::read8(v, buf);
+    F::run(v, buf, tw);
+    const T nrm = (T)sqrt(2.0 / N);
+    const T half = (T)0.70710678118654752440;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int j = t + e * NT;
+        const int m = (BC == DIR) ? N - 1 - j : j;
+        const cx<T> zm = buf[F::at(m)];
+        const cx<T> w = ld_tw<T>(pt, m);
+        const T sc = nrm * (m == 0 ? half : (T)1);
+        if constexpr (ROWS == 2) {
+            // Z = V0 + i V1: V0_m = (Z_m + conj Z_{N-m}) / 2, V1_m = (Z_m - conj Z_{N-m}) / 2i
+            const cx<T> zc = buf[F::at((N - m) & (N - 1))];
+            const T v0x = (T)0.5 * (zm.x + zc.x), v0y = (T)0.5 * (zm.y - zc.y);
+            const T v1x = (T)0.5 * (zm.y + zc.y), v1y = (T)0.5 * (zc.x - zm.x);
+            s0[e] = sc * (v0x * w.x - v0y * w.y);
+            s1[e] = sc * (v1x * w.x - v1y * w.y);
+        } else {
+            s0[e] = sc * (zm.x * w.x - zm.y * w.y);
+            s1[e] = (T)0;
+        }
+        in_register(s0[e]);
+        in_register(s1[e]);
+    }
+}
+
 // Forward transform of rows i0 .. i0 + ROWS - 1 (the last workgroup of an odd
 // nr has one): fused PCG step or plain, as zfwd_body.
 template <typename T, int BC, bool FUSED, int N, int ROWS>
@@ -160,45 +216,125 @@ __device__ __forceinline__ void zfwd8_body(const double *__restrict__ rin, doubl
             }
         }
     }
-    // even k -> v[k/2], odd k -> v[N-1-(k-1)/2] (sine: y_k = (-1)^k x_k); the
-    // second row in the imaginary parts
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int n = t + j * NT;
-        const T sg = (BC == DIR) ? (T)-1 : (T)1;
-        buf[F::at(n)] = {(T)rv[0][j].x, two ? (T)rv[ROWS - 1][j].x : (T)0};
-        buf[F::at(N - 1 - n)] = {sg * (T)rv[0][j].y, two ? sg * (T)rv[ROWS - 1][j].y : (T)0};
-    }
-    __syncthreads();
-    cx<T> v[8];
-    F::read8(v, buf);
-    F::run(v, buf, tw);
-    const T nrm = (T)sqrt(2.0 / N);
-    const T half = (T)0.70710678118654752440;
+    T s0[8], s1[8];
+    pair_spectra<T, BC, N, ROWS>(rv[0], rv[ROWS - 1], two, buf, tw, pt, s0, s1);
     T *row0 = spec + (size_t)i0 * N;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const int j = t + e * NT;
-        const int m = (BC == DIR) ? N - 1 - j : j;
-        const cx<T> zm = buf[F::at(m)];
-        const cx<T> w = ld_tw<T>(pt, m);
-        const T sc = nrm * (m == 0 ? half : (T)1);
-        if constexpr (ROWS == 2) {
-            // Z = V0 + i V1: V0_m = (Z_m + conj Z_{N-m}) / 2, V1_m = (Z_m - conj Z_{N-m}) / 2i
-            const cx<T> zc = buf[F::at((N - m) & (N - 1))];
-            const T v0x = (T)0.5 * (zm.x + zc.x), v0y = (T)0.5 * (zm.y - zc.y);
-            const T v1x = (T)0.5 * (zm.y + zc.y), v1y = (T)0.5 * (zc.x - zm.x);
-            row0[j] = sc * (v0x * w.x - v0y * w.y);
-            if (two) row0[N + j] = sc * (v1x * w.x - v1y * w.y);
-        } else {
-            row0[j] = sc * (zm.x * w.x - zm.y * w.y);
-        }
+        row0[t + e * NT] = s0[e];
+        if (two) row0[N + t + e * NT] = s1[e];
     }
     if (FUSED) {
         const double s = block_sum(rr, red);
         if (threadIdx.x == 0) partials[SLOT_RR * MAX_PARTIALS + vb] = s;
     }
 }
+
+// The inverse FFT of one row's or two rows' spectra: pair_stage puts them
+// (modes t + e NT in y0, y1) into the free buffer as unnormalised DCT-II
+// coefficients Y_m; pair_inverse leaves N times the rows, reordered, in the
+// buffer's real and imaginary parts.
+template <typename T, int BC, int N>
+__device__ __forceinline__ void pair_stage(const T (&y0)[8], const T (&y1)[8], cx<T> *buf)
+{
+    using F = BlockFft<T, N>;
+    const T isc = (T)sqrt(0.5 * N);      // 1 / sqrt(2/N)
+    const T sq2 = (T)1.41421356237309504880;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int j = (int)threadIdx.x + e * F::NT;
+        const int m = (BC == DIR) ? N - 1 - j : j;
+        const T sc = isc * (m == 0 ? sq2 : (T)1);
+        buf[F::at(m)] = {y0[e] * sc, y1[e] * sc};
+    }
+}
+
+template <typename T, int N, int ROWS>
+__device__ __forceinline__ void pair_inverse(cx<T> *buf, const typename vec2_of<T>::type *__restrict__ tw,
+                                             const typename vec2_of<T>::type *__restrict__ pt)
+{
+    using F = BlockFft<T, N>;
+    constexpr int NT = F::NT;
+    const int t = threadIdx.x;
+    __syncthreads();
+    // the FFT of conj(V0) + i conj(V1), conj(V)_m = w_m (Y_m + i Y_{N-m})
+    cx<T> v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int m = t + e * NT;
+        const cx<T> y = buf[F::at(m)];
+        const cx<T> yn = (m == 0) ? cx<T>{(T)0, (T)0} : buf[F::at((N - m) & (N - 1))];
+        const cx<T> w = ld_tw<T>(pt, m);
+        const cx<T> q0 = {w.x * y.x - w.y * yn.x, w.x * yn.x + w.y * y.x};
+        if constexpr (ROWS == 2) {
+            const cx<T> q1 = {w.x * y.y - w.y * yn.y, w.x * yn.y + w.y * y.y};
+            v[e] = {q0.x - q1.y, q0.y + q1.x};
+        } else {
+            v[e] = q0;
+        }
+    }
+    F::run(v, buf, tw);
+}
+
+// What an inverse transform of a row or a pair of rows reads besides its
+// spectra (r and the old z, or the increment; in flight during the FFT) and
+// its results' way out of the buffer (pair_inverse), as pairs of columns.
+template <typename T, int MODE, int N>
+struct RowPair {
+    static constexpr bool PCGM = (MODE == 1 || MODE == 2);
+    static constexpr bool CHEB = (MODE == 3 || MODE == 4);
+    static constexpr int NT = N / 8;
+    double2 rv[2][4], zo[2][4];
+    __device__ __forceinline__ void load(const ZOut<T, MODE> *zout, const double *r, const double *dinc, bool pr, int i,
+                                         bool two)
+    {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if (s && !two) continue;
+            const size_t base = (size_t)(i + s) * N + 2 * threadIdx.x;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (PCGM) {
+                    rv[s][j] = *reinterpret_cast<const double2 *>(r + base + 2 * j * NT);
+                    if (pr) zo[s][j] = ld_pair(zout + base + 2 * j * NT);
+                }
+                if (MODE == 3) rv[s][j] = *reinterpret_cast<const double2 *>(dinc + base + 2 * j * NT);
+            }
+        }
+    }
+    template <int BC, int ROWS>
+    __device__ __forceinline__ void store(const cx<T> *buf, ZOut<T, MODE> *zout, double *dinc, bool pr, int i, bool two,
+                                          double c1, double c2, double &rz, double &rzo) const
+    {
+        using F = BlockFft<T, N>;
+        const int t = threadIdx.x;
+        const T invN = (T)1 / (T)N;
+        const T sg = (BC == DIR) ? -invN : invN;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int n = t + j * NT;
+            const cx<T> ev = buf[F::at(n)], od = buf[F::at(N - 1 - n)];
+#pragma unroll
+            for (int s = 0; s < ROWS; ++s) {
+                if (s && !two) continue;
+                const double2 zv = make_double2((double)((s ? ev.y : ev.x) * invN), (double)((s ? od.y : od.x) * sg));
+                const size_t base = (size_t)(i + s) * N + 2 * t + 2 * j * NT;
+                if (PCGM) {
+                    if (pr) rzo += rv[s][j].x * zo[s][j].x + rv[s][j].y * zo[s][j].y;
+                    rz += rv[s][j].x * zv.x + rv[s][j].y * zv.y;
+                }
+                if (CHEB) {
+                    const double2 d = rv[s][j];
+                    *reinterpret_cast<double2 *>(dinc + base) =
+                        (MODE == 4) ? make_double2(c2 * zv.x, c2 * zv.y)
+                                    : make_double2(c1 * d.x + c2 * zv.x, c1 * d.y + c2 * zv.y);
+                } else {
+                    st_pair(zout + base, zv);
+                }
+            }
+        }
+    }
+};
 
 // Inverse transform of the same rows, modes as zinv_body.
 template <typename T, int BC, int MODE, int N, int ROWS>
@@ -220,31 +356,16 @@ __device__ __forceinline__ void zinv8_body(const T *__restrict__ spec, ZOut<T, M
     const int t = threadIdx.x;
     const bool two = ROWS == 2 && i0 + 1 < nr;
     const int done = MODE != 0 ? st->done : 0;
-    // unnormalised DCT-II coefficients Y_m of both rows into the buffer
-    const T isc = (T)sqrt(0.5 * N);      // 1 / sqrt(2/N)
-    const T sq2 = (T)1.41421356237309504880;
+    T y0[8], y1[8];
     const T *s0 = spec + (size_t)i0 * N, *s1 = s0 + (two ? N : 0);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const int m = t + e * NT;
-        const int j = (BC == DIR) ? N - 1 - m : m;
-        const T sc = isc * (m == 0 ? sq2 : (T)1);
-        buf[F::at(m)] = {s0[j] * sc, ROWS == 2 ? s1[j] * sc : (T)0};
+        y0[e] = s0[t + e * NT];
+        y1[e] = ROWS == 2 ? s1[t + e * NT] : (T)0;
     }
-    // r (and the old z, or the increment) of the rows are in flight during the FFT
-    double2 rv[ROWS][4], zo[ROWS][4];
-#pragma unroll
-    for (int s = 0; s < ROWS; ++s) {
-        const size_t base = (size_t)(i0 + (s && !two ? 0 : s)) * N + 2 * t;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (PCGM) {
-                rv[s][j] = *reinterpret_cast<const double2 *>(r + base + 2 * j * NT);
-                if (pr) zo[s][j] = ld_pair(zout + base + 2 * j * NT);
-            }
-            if (MODE == 3) rv[s][j] = *reinterpret_cast<const double2 *>(dinc + base + 2 * j * NT);
-        }
-    }
+    pair_stage<T, BC, N>(y0, y1, buf);
+    RowPair<T, MODE, N> io;
+    io.load(zout, r, dinc, pr, i0, two);
     if (done) {   // every workgroup alike
         if (MODE == 1) x_finish(fin, st, (size_t)i0 * N, (two ? 2 : 1) * N, t, NT);
         return;
@@ -255,51 +376,9 @@ __device__ __forceinline__ void zinv8_body(const T *__restrict__ spec, ZOut<T, M
         c1 = alpha - 1.0;
         c2 = alpha * tau;
     }
-    __syncthreads();
-    // the FFT of conj(V0) + i conj(V1), conj(V)_m = w_m (Y_m + i Y_{N-m}), whose
-    // real and imaginary parts are N times the two rows
-    cx<T> v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int m = t + e * NT;
-        const cx<T> y = buf[F::at(m)];
-        const cx<T> yn = (m == 0) ? cx<T>{(T)0, (T)0} : buf[F::at((N - m) & (N - 1))];
-        const cx<T> w = ld_tw<T>(pt, m);
-        const cx<T> q0 = {w.x * y.x - w.y * yn.x, w.x * yn.x + w.y * y.x};
-        if constexpr (ROWS == 2) {
-            const cx<T> q1 = {w.x * y.y - w.y * yn.y, w.x * yn.y + w.y * y.y};
-            v[e] = {q0.x - q1.y, q0.y + q1.x};
-        } else {
-            v[e] = q0;
-        }
-    }
-    F::run(v, buf, tw);
-    const T invN = (T)1 / (T)N;
-    const T sg = (BC == DIR) ? -invN : invN;
+    pair_inverse<T, N, ROWS>(buf, tw, pt);
     double rz = 0.0, rzo = 0.0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int n = t + j * NT;
-        const cx<T> ev = buf[F::at(n)], od = buf[F::at(N - 1 - n)];
-#pragma unroll
-        for (int s = 0; s < ROWS; ++s) {
-            if (s && !two) continue;
-            const double2 zv = make_double2((double)((s ? ev.y : ev.x) * invN), (double)((s ? od.y : od.x) * sg));
-            const size_t base = (size_t)(i0 + s) * N + 2 * t + 2 * j * NT;
-            if (PCGM) {
-                if (pr) rzo += rv[s][j].x * zo[s][j].x + rv[s][j].y * zo[s][j].y;
-                rz += rv[s][j].x * zv.x + rv[s][j].y * zv.y;
-            }
-            if (CHEB) {
-                const double2 d = rv[s][j];
-                *reinterpret_cast<double2 *>(dinc + base) =
-                    (MODE == 4) ? make_double2(c2 * zv.x, c2 * zv.y)
-                                : make_double2(c1 * d.x + c2 * zv.x, c1 * d.y + c2 * zv.y);
-            } else {
-                st_pair(zout + base, zv);
-            }
-        }
-    }
+    io.template store<BC, ROWS>(buf, zout, dinc, pr, i0, two, c1, c2, rz, rzo);
     if (PCGM) {
         const double s = block_sum(rz, red);
         if (threadIdx.x == 0) partials[SLOT_RZ * MAX_PARTIALS + vb] = s;

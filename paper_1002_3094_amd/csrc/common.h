@@ -99,6 +99,10 @@ struct PfPlan {
     void *fn = nullptr;
 };
 
+// Rows of the r-line arrays and the spectral buffer: nr up to whole strips of
+// eight rows.
+__host__ __device__ inline int line_rows(int nr) { return (nr + 7) & ~7; }
+
 struct Operator {
     int nr = 0, nz = 0, bc_z = 0;
     bool nodes = false;              // the paper's node grid (AXIPCG_GRID_NODES)
@@ -121,6 +125,8 @@ struct Operator {
     //   db[i]  = r-part of the diagonal (cb[i] + cb[i-1], outer face doubled)
     //   rw[i]  = r_i
     //   lam[j] = kbar mu_j + qbar (mode j)
+    // the r-line arrays are padded to line_rows(nr) rows with cb = rw = 0,
+    // db = 1 (uncoupled rows whose solution is their right-hand side)
     double *cb64 = nullptr, *db64 = nullptr, *rw64 = nullptr, *lam64 = nullptr;
     float *cb32 = nullptr, *db32 = nullptr, *rw32 = nullptr, *lam32 = nullptr;
     // FFT tables for length nz: tw[k] = exp(-2 pi i k / nz), pt[m] = exp(-i pi m / (2 nz))
@@ -129,7 +135,7 @@ struct Operator {
 
     // PCG workspace (device)
     double *r = nullptr, *z = nullptr, *p0 = nullptr, *p1 = nullptr, *q = nullptr;
-    void *spec = nullptr;          // spectral buffer, nr*nz doubles (used as float or double)
+    void *spec = nullptr;          // spectral buffer, line_rows(nr)*nz doubles (used as float or double)
     double *partials = nullptr;    // [PARTIAL_ROWS][MAX_PARTIALS] per-workgroup partial sums
     PcgState *state = nullptr;
     double *dscal = nullptr;         // 24 device scalars: residual norms [0..1], the guard [8..16]
@@ -141,7 +147,7 @@ struct Operator {
     double *scratch_host = nullptr;  // pinned host scalars (16)
 
     // strip-partitioned preconditioner (strip.hip): reduced data of the strips
-    // (three [nr / R][nz] arrays, used as float or double); on unless disabled
+    // (three [ceil(nr / R)][nz] arrays, used as float or double); on unless disabled
     void *strip_red = nullptr;
     int strip_rows = 4;   // strip height (4 or 8), 0 = the per-mode r-solve instead
 

@@ -40,8 +40,9 @@ k_zfwd8(const double *__restrict__ rin, double *__restrict__ r, const double *__
     zfwd8_body<T, BC, FUSED, N, ROWS>(rin, r, q, st, partials, n_pq, spec, tw, pt, nr, blockIdx.x);
 }
 
+// (four waves per SIMD in FP32: two workgroups of 512 threads per CU)
 template <typename T, int BC, int MODE, int N, int ROWS>
-__global__ void __launch_bounds__(N / 8)
+__global__ void __launch_bounds__(N / 8, sizeof(T) == 4 ? 4 : 1)
 k_zinv8(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout, const double *__restrict__ r,
         const PcgState *st, double *__restrict__ partials, bool pr,
         const typename vec2_of<T>::type *__restrict__ tw, const typename vec2_of<T>::type *__restrict__ pt, int nr,
@@ -463,7 +464,8 @@ int strip_solve_rows(const Operator &op, int prec)
 
 int transform_blocks(const Operator &op, int prec)
 {
-    if (strip_usable(op, prec, strip_solve_rows(op, prec))) return op.nr / strip_solve_rows(op, prec);
+    const int sr = strip_solve_rows(op, prec);
+    if (strip_usable(op, prec, sr)) return (op.nr + sr - 1) / sr;
     const int wr = (prec == AXIPCG_PREC_FP32) ? wave_plan_rows<float>(op.nz) : wave_plan_rows<double>(op.nz);
     if (wr > 0) return (op.nr + wr - 1) / wr;
     const int rows = transform_rows(op.nr, op.nz, prec);
@@ -659,7 +661,7 @@ void launch_tridiag(const Operator &op, int prec, const TriGate &g, hipStream_t 
 void precond_apply_impl(const Operator &op, const double *r, double *z, int prec, hipStream_t s)
 {
     int rows = strip_solve_rows(op, prec);
-    if (rows == 4 && prec == AXIPCG_PREC_FP32 && op.nz == 2048 && strip_usable(op, prec, 8)) rows = 8;
+    if (rows == 4 && prec == AXIPCG_PREC_FP32 && op.nz == 2048 && op.nr % 8 == 0 && strip_usable(op, prec, 8)) rows = 8;
     if (rows > 0 && strip_usable(op, prec, rows)) {
         ZfwdArgs fa;
         fa.rin = r;

@@ -94,6 +94,12 @@ __global__ void k_tables(Operator op, double kbar, double qbar, double rb)
     const double hr = op.hr, hz = op.hz;
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
     const int nthr = gridDim.x * blockDim.x;
+    for (int i = nr + tid; i < line_rows(nr); i += nthr) {
+        op.cb64[i] = op.rw64[i] = 0.0;
+        op.db64[i] = 1.0;
+        op.cb32[i] = op.rw32[i] = 0.f;
+        op.db32[i] = 1.f;
+    }
     for (int i = tid; i < nr; i += nthr) {
         const double cbi = (i < nr - 1) ? (i + 1) * hr * kbar / (hr * hr) : 0.0;
         const double up = (i < nr - 1) ? cbi : rb * nr * hr * kbar / (hr * hr);
@@ -261,16 +267,16 @@ Operator *create_impl(int nr, int nz, double lr, double lz, int bc_z, const doub
         op->create_stream = s;
         AXI_CHECK_HIP(hipGetDevice(&op->device));
         dmalloc(&op->D, n); dmalloc(&op->CR, n); dmalloc(&op->CZ, n); dmalloc(&op->W, n);
-        dmalloc(&op->cb64, nr); dmalloc(&op->db64, nr); dmalloc(&op->rw64, nr); dmalloc(&op->lam64, nz);
-        dmalloc(&op->cb32, nr); dmalloc(&op->db32, nr); dmalloc(&op->rw32, nr); dmalloc(&op->lam32, nz);
+        const int nrp = line_rows(nr);
+        dmalloc(&op->cb64, nrp); dmalloc(&op->db64, nrp); dmalloc(&op->rw64, nrp); dmalloc(&op->lam64, nz);
+        dmalloc(&op->cb32, nrp); dmalloc(&op->db32, nrp); dmalloc(&op->rw32, nrp); dmalloc(&op->lam32, nz);
         dmalloc(&op->tw64, nz); dmalloc(&op->pt64, nz); dmalloc(&op->tw32, nz); dmalloc(&op->pt32, nz);
         dmalloc(&op->r, n); dmalloc(&op->z, n); dmalloc(&op->p0, n); dmalloc(&op->p1, n); dmalloc(&op->q, n);
-        dmalloc((double **)&op->spec, n);
+        dmalloc((double **)&op->spec, (size_t)nrp * nz);
         dmalloc(&op->partials, (size_t)PARTIAL_ROWS * MAX_PARTIALS);
         dmalloc(&op->state, 1);
         dmalloc(&op->dscal, 24);
-        if (const size_t sb = strip_red_bytes(nr, nz))
-            AXI_CHECK_HIP(hipMalloc(&op->strip_red, sb));
+        AXI_CHECK_HIP(hipMalloc(&op->strip_red, strip_red_bytes(nr, nz)));
         AXI_CHECK_HIP(hipMalloc((void **)&op->pf_bar, (1 + 1024) * sizeof(unsigned)));
         AXI_CHECK_HIP(hipMalloc((void **)&op->pf_err, sizeof(int)));
         AXI_CHECK_HIP(hipMemsetAsync(op->pf_bar, 0, (1 + 1024) * sizeof(unsigned), s));
@@ -522,7 +528,7 @@ int axipcg_op_strips_info(axipcg_op_t h, int prec, int *active, int *strips)
         const int rows = strip_solve_rows(*op, prec);
         const bool ok = rows > 0 && strip_usable(*op, prec, rows);
         if (active) *active = ok ? 1 : 0;
-        if (strips) *strips = ok ? op->nr / rows : 0;
+        if (strips) *strips = ok ? (op->nr + rows - 1) / rows : 0;
         return AXIPCG_OK;
     });
 }

@@ -56,6 +56,10 @@ strip_phase1(const double *__restrict__ rin, double *__restrict__ r, const doubl
     if (!zfwd_w_body<T, BC, FUSED, R2>(rin, r, q, st, partials, n_pq, tw, pt, nr, i0 + wv, s,
                                         RowStore<T>{tile + wv * PITCH}))
         return false;
+    // a row past the last one (nr no multiple of R): right-hand side zero on an
+    // uncoupled line of the padded r-line arrays
+    if (i0 + wv >= nr)
+        for (int l = threadIdx.x & 63; l < N; l += 64) tile[wv * PITCH + l] = (T)0;
     if constexpr (FUSED) load_lines();
     __syncthreads();
 #pragma unroll
@@ -237,6 +241,7 @@ __host__ __device__ inline size_t strip_red_lds(int nr, int G, int mt)
     return (3 * (size_t)(nr + nr / 32 + 1) + 2 * (size_t)mt * G) * sizeof(T);
 }
 
+// (nr here and in strip_solve2: G strips' rows, the padded ones included.)
 // Phase 2 (K2) part 1: stage the r-line arrays and the reduced data of modes
 // [l0, l0 + mt) into LDS (`base`); vector loads when the mt values of a
 // strip's row are 16-byte pieces.
@@ -370,7 +375,8 @@ strip_phase3(const T *__restrict__ fprime, const T *__restrict__ red_x, ZOut<T, 
     if constexpr (PRE) {
 #pragma unroll
         for (int t = 0; t < R2; ++t)
-            rpre[t] = *reinterpret_cast<const double2 *>(r + (size_t)(i0 + wv) * N + 2 * lane + 128 * t);
+            rpre[t] = *reinterpret_cast<const double2 *>(r + (size_t)(i0 + wv < nr ? i0 + wv : nr - 1) * N +
+                                                         2 * lane + 128 * t);
     }
     // this thread's modes' eigenvalues and reduced solutions X_s, X_{s-1}
     // (the previous launch's output), issued with the row loads instead of
@@ -406,7 +412,7 @@ strip_phase3(const T *__restrict__ fprime, const T *__restrict__ red_x, ZOut<T, 
     // a stopped solve (every workgroup alike) returns here, its loads already
     // issued rather than waiting on the flag before them
     if (MODE != 0 && st->done) {
-        if (MODE == 1) x_finish(fin, st, (size_t)i0 * N, R * N, threadIdx.x, NT);
+        if (MODE == 1) x_finish(fin, st, (size_t)i0 * N, (nr - i0 < R ? nr - i0 : R) * N, threadIdx.x, NT);
         return;
     }
     __syncthreads();

@@ -38,6 +38,9 @@
 //     a_s = -cb[j-1] v'_{n-1},  b_s = D_j - cb[j-1] c'_{n-1} - cb[j] v_0(s+1),
 //     c_s = -cb[j] w_0(s+1),    e_s = E1_s + cb[j] G0_{s+1},
 //     E1_s = f_j + cb[j-1] f'_{n-1}.
+// When R does not divide nr the last strip's missing rows are uncoupled lines
+// with a zero right-hand side (the r-line arrays are padded so), which changes
+// no other row.
 // The coefficient-only quantities (c', v', v_0, w_0) are recomputed where
 // needed from the O(nr) r-line arrays instead of being stored.
 #include "strip.h"
@@ -89,6 +92,8 @@ k_strip_inv(const T *__restrict__ fprime, const T *__restrict__ red_x, ZOut<T, M
                                      blockIdx.x, reinterpret_cast<T *>(smem_raw), fin);
 }
 
+inline int strip_count(int nr, int R) { return (nr + R - 1) / R; }
+
 template <typename T>
 Lines<T> lines_of(const Operator &op);
 template <>
@@ -117,7 +122,7 @@ template <typename T>
 RedBufs<T> red_bufs(const Operator &op, int R)
 {
     T *b = static_cast<T *>(op.strip_red);
-    const size_t gn = (size_t)(op.nr / R) * op.nz;
+    const size_t gn = (size_t)strip_count(op.nr, R) * op.nz;
     return {b, b + gn, b + 2 * gn};
 }
 
@@ -140,7 +145,9 @@ int red_mt_for(int nr, int G)
 void allow_lds(const void *fn, size_t bytes, bool &done)
 {
     if (done || bytes <= 65536) return;
-    AXI_CHECK_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    // (the kernels' own static LDS is under 1 KiB of the 160)
+    const int most = 159 * 1024;
+    AXI_CHECK_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes < most ? most : (int)bytes));
     done = true;
 }
 
@@ -148,7 +155,7 @@ template <typename T, int BC, int R2, int R>
 void fwd_r(const Operator &op, const ZfwdArgs &a, hipStream_t s)
 {
     const RedBufs<T> rb = red_bufs<T>(op, R);
-    const dim3 grid(op.nr / R), block(64 * R);
+    const dim3 grid(strip_count(op.nr, R)), block(64 * R);
     const size_t shm = (size_t)R * wfft::Geo<R2>::LB * sizeof(cx<T>);
     if (a.fused)
         hipLaunchKernelGGL((k_strip_fwd<T, BC, true, R2, R>), grid, block, shm, s, nullptr, a.r, a.q, a.state, op.partials, a.n_pq, (T *)op.spec, rb.e, rb.g, tw_of<T>(op), pt_of<T>(op),
@@ -163,7 +170,7 @@ template <typename T, int BC, int R2, int R>
 void inv_r(const Operator &op, const ZinvArgs &a, hipStream_t s)
 {
     const RedBufs<T> rb = red_bufs<T>(op, R);
-    const dim3 grid(op.nr / R), block(64 * R);
+    const dim3 grid(strip_count(op.nr, R)), block(64 * R);
     const size_t shm = (size_t)R * wfft::Geo<R2>::LB * sizeof(cx<T>);
     const T *fp = (const T *)op.spec;
     const auto tw = tw_of<T>(op);
@@ -188,19 +195,19 @@ template <typename T, int R, int LM, int MT>
 void red_launch_mt(const Operator &op, const TriGate &g, hipStream_t s)
 {
     const RedBufs<T> rb = red_bufs<T>(op, R);
-    const int G = op.nr / R;
-    const size_t shm = strip_red_lds<T>(op.nr, G, MT);
+    const int G = strip_count(op.nr, R), rows = G * R;
+    const size_t shm = strip_red_lds<T>(rows, G, MT);
     static bool lds_set = false;
     allow_lds(reinterpret_cast<const void *>(&k_strip_reduced<T, R, LM, MT>), shm, lds_set);
     hipLaunchKernelGGL((k_strip_reduced<T, R, LM, MT>), dim3(op.nz / MT), dim3(64 * MT), shm, s, rb.e, rb.g, rb.x,
-                       lines_of<T>(op), g.state, op.partials, g, op.nr, op.nz, G);
+                       lines_of<T>(op), g.state, op.partials, g, rows, op.nz, G);
     AXI_CHECK_HIP(hipGetLastError());
 }
 
 template <typename T, int R, int LM>
 void red_launch(const Operator &op, const TriGate &g, hipStream_t s)
 {
-    const int mt = red_mt_for<T>(op.nr, op.nr / R);
+    const int G = strip_count(op.nr, R), mt = red_mt_for<T>(G * R, G);
     if (mt >= 8) red_launch_mt<T, R, LM, (red_mt<T>() >= 8 ? 8 : 2)>(op, g, s);
     else if (mt >= 4) red_launch_mt<T, R, LM, 4>(op, g, s);
     else red_launch_mt<T, R, LM, 2>(op, g, s);
@@ -209,7 +216,7 @@ void red_launch(const Operator &op, const TriGate &g, hipStream_t s)
 template <typename T, int R>
 void red_r(const Operator &op, const TriGate &g, hipStream_t s)
 {
-    const int per = (op.nr / R + 63) / 64;
+    const int per = (strip_count(op.nr, R) + 63) / 64;
     if (per <= 1) red_launch<T, R, 1>(op, g, s);
     else if (per <= 2) red_launch<T, R, 2>(op, g, s);
     else if (per <= 4) red_launch<T, R, 4>(op, g, s);
@@ -285,16 +292,15 @@ template <typename T>
 bool usable_t(const Operator &op, int R)
 {
     if (R != 4 && R != 8) return false;
-    if (strip_r2<T>(op.nz) == 0 || op.nr % R != 0) return false;
-    const int G = op.nr / R;
-    return G >= 1 && G <= 1024 && strip_red_lds<T>(op.nr, G, red_mt_for<T>(op.nr, G)) <= 160 * 1024;
+    if (strip_r2<T>(op.nz) == 0) return false;
+    const int G = strip_count(op.nr, R), rows = G * R;
+    return G <= 1024 && strip_red_lds<T>(rows, G, red_mt_for<T>(rows, G)) <= 160 * 1024;
 }
 
 }  // namespace
 
 // The strip path serves an operator and precision with strips of `rows`
-// rows (4 or 8) when the one-wave transforms cover nz, the rows split into
-// such strips and the reduced system fits one wavefront's registers (at most
+// rows (4 or 8) when the one-wave transforms cover nz and the reduced system fits one wavefront's registers (at most
 // 1024 strips) and its workgroup's LDS.
 bool strip_usable(const Operator &op, int prec, int rows)
 {
@@ -305,7 +311,7 @@ bool strip_usable(const Operator &op, int prec, int rows)
 // Reduced data for strips of 4 rows (the larger of the two heights' needs).
 size_t strip_red_bytes(int nr, int nz)
 {
-    return (nr % 4 == 0) ? 3 * (size_t)(nr / 4) * nz * sizeof(double) : 0;
+    return 3 * (size_t)strip_count(nr, 4) * nz * sizeof(double);
 }
 
 void strip_fwd(const Operator &op, int prec, int rows, const ZfwdArgs &a, hipStream_t s)
