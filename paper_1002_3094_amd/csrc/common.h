@@ -149,6 +149,8 @@ struct Operator {
     // strip-partitioned preconditioner (strip.hip): reduced data of the strips
     // (three [ceil(nr / R)][nz] arrays, used as float or double); on unless disabled
     void *strip_red = nullptr;
+    float *red_fac32 = nullptr;    // factors of the reduced systems (strip.h, RedFac), where the
+    double *red_fac64 = nullptr;   // strips' transforms cover nz in that precision
     int strip_rows = 4;   // strip height (4 or 8), 0 = the per-mode r-solve instead
 
     // single-launch preconditioner (pfused.hip): plans [standalone, PCG]

@@ -82,6 +82,8 @@ bool strip_usable(const Operator &op, int prec, int rows);
 // The strip height of the solves' launches for this precision (0: per-mode).
 int strip_solve_rows(const Operator &op, int prec);
 size_t strip_red_bytes(int nr, int nz);
+// Allocates and fills the factors of the reduced systems (op.red_fac32, _64).
+void strip_factors(Operator &op, hipStream_t s);
 void strip_fwd(const Operator &op, int prec, int rows, const ZfwdArgs &a, hipStream_t s);
 void strip_reduced(const Operator &op, int prec, int rows, const TriGate &g, hipStream_t s);
 void strip_inv(const Operator &op, int prec, int rows, const ZinvArgs &a, hipStream_t s);

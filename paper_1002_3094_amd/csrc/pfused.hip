@@ -45,6 +45,7 @@ struct OneArgs {
     XFin fin;
     const typename vec2_of<T>::type *tw, *pt;
     Lines<T> ln;
+    const T *fac;
     int nr, G, mpw;
     unsigned *bar;
     int *err;
@@ -86,7 +87,20 @@ __global__ void __launch_bounds__(64 * R) k_strip_one(OneArgs<T> A)
         return;
     }
     const int l0 = s * A.mpw, cnt = N - l0 < A.mpw ? N - l0 : A.mpw;
-    if (cnt > 0) {
+    if (cnt > 0 && R == 4) {
+        // the factored systems, in the operations of the three-launch form
+        stage_red<T, false>(A.red_e, A.red_g, N, A.G, l0, cnt, base2);
+        __syncthreads();
+        const int lane = threadIdx.x & 63;
+        int S, lo, m;
+        red_lane(A.G, lane, S, lo, m);
+        for (int w = threadIdx.x >> 6; w < cnt; w += R) {
+            RedFac<T, LMAX> f;
+            f.load(A.fac, l0 + w, red_rows(A.G), A.ln.cb, lo, m, lane);
+            f.solve(base2 + w * A.G, base2 + (cnt + w) * A.G, A.G, lo, m, S, lane);
+        }
+        store_red<T, false>(A.red_x, N, A.G, l0, cnt, base2);
+    } else if (cnt > 0) {
         strip_stage2<T, false>(A.red_e, A.red_g, A.ln, A.nr, N, A.G, l0, cnt, base2);
         __syncthreads();
         strip_solve2<T, R, LMAX, false>(A.red_x, A.ln, A.nr, N, A.G, l0, cnt, base2);
@@ -171,6 +185,7 @@ static OneArgs<float> one_args(Operator &op, const PfPlan &pl)
     a.tw = op.tw32;
     a.pt = op.pt32;
     a.ln = {op.cb32, op.db32, op.rw32, op.lam32};
+    a.fac = op.red_fac32;
     a.nr = op.nr;
     a.G = pl.G;
     a.mpw = pl.L2;

@@ -208,7 +208,7 @@ void free_op(Operator *op)
     void *ptrs[] = {op->D, op->CR, op->CZ, op->W, op->cb64, op->db64, op->rw64, op->lam64, op->cb32,
                     op->db32, op->rw32, op->lam32, op->tw64, op->pt64, op->tw32, op->pt32, op->r,
                     op->z, op->p0, op->p1, op->q, op->spec, op->partials, op->state, op->dscal,
-                    op->pf_bar, op->pf_err, op->strip_red};
+                    op->pf_bar, op->pf_err, op->strip_red, op->red_fac32, op->red_fac64};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (hipEvent_t e : op->prof_events) (void)hipEventDestroy(e);
@@ -361,6 +361,7 @@ Operator *create_impl(int nr, int nz, double lr, double lz, int bc_z, const doub
         const int tb = (nr > nz ? nr : nz);
         hipLaunchKernelGGL(k_tables, dim3((tb + 255) / 256), dim3(256), 0, s, *op, kb, qb, nodes ? 1.0 : 2.0);
         AXI_CHECK_HIP(hipGetLastError());
+        strip_factors(*op, s);
         AXI_CHECK_HIP(hipStreamSynchronize(s));
     } catch (...) {
         free_op(op);

@@ -233,6 +233,114 @@ __device__ inline void wave_tri(const T (&a)[LMAX], const T (&b)[LMAX], const T 
     }
 }
 
+// ---------------------------------------------------------------------------
+// The reduced systems of strips of four rows with their coefficients factored
+// once per operator (strip_factors, strip.hip): what depends on the operator
+// and the mode alone -- the strips' preparatory solutions, the pivots of each
+// lane's rows and the multipliers of the cyclic reduction -- is read instead of
+// being recomputed in every solve, so that a solve only carries right-hand
+// sides: two shuffles per reduction level instead of eight, no reciprocals and
+// no r-line arrays in LDS.
+//
+// The reduced matrix is symmetric, a_{k+1} = c_k, and stored so.  Factors of
+// mode l, lane `lane` and item k at fac[(l red_items(L) + k) 64 + lane], L the
+// rows per lane the layout was made for: inv[L - 1], c[L], a_0, al[6], ga[6],
+// 1 / (the lane's reduced pivot).
+// ---------------------------------------------------------------------------
+__host__ __device__ inline int red_items(int L) { return 2 * L + 13; }
+// Rows per lane of G strips, up to a power of two (the kernels' register rows).
+__host__ __device__ inline int red_rows(int G)
+{
+    int L = 1;
+    while (64 * L < G) L *= 2;
+    return L;
+}
+
+template <typename T, int LMAX>
+struct RedFac {
+    T inv[LMAX], c[LMAX], cj[LMAX], a0, al[6], ga[6], piv;
+    // rows [lo, lo + m) of the lane; L the layout's rows per lane (L <= LMAX);
+    // cj: the couplings of the interface rows to the next strips
+    __device__ __forceinline__ void load(const T *__restrict__ fac, int l, int L, const T *__restrict__ cb, int lo,
+                                         int m, int lane)
+    {
+        const T *f = fac + (size_t)l * red_items(L) * 64 + lane;
+#pragma unroll
+        for (int t = 0; t < LMAX; ++t) {
+            inv[t] = t < L - 1 ? f[t * 64] : (T)0;
+            c[t] = t < L ? f[(L - 1 + t) * 64] : (T)0;
+            cj[t] = t < m ? cb[(lo + t) * 4 + 3] : (T)0;
+        }
+        f += (2 * L - 1) * 64;
+        a0 = f[0];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            al[k] = f[(1 + k) * 64];
+            ga[k] = f[(7 + k) * 64];
+        }
+        piv = f[13 * 64];
+    }
+    // te, tg: E1 and G0 of the mode's strips (LDS); the solution replaces te
+    // (every lane has read its values of te before any is written).
+    __device__ __forceinline__ void solve(T *te, const T *tg, int G, int lo, int m, int S, int lane) const
+    {
+        const bool active = lane < S;
+        T gp[LMAX], vp[LMAX], cq[LMAX], e[LMAX];
+#pragma unroll
+        for (int t = 0; t < LMAX; ++t)
+            e[t] = t < m ? te[lo + t] + (lo + t + 1 < G ? cj[t] * tg[lo + t + 1] : (T)0) : (T)0;
+        T gl = 0, em = 0, am = 0, cm = 0;
+#pragma unroll
+        for (int t = 0; t < LMAX; ++t) {
+            if (t < m - 1) {
+                gp[t] = (t == 0 ? e[0] : e[t] - c[t - 1] * gp[t - 1]) * inv[t];
+                vp[t] = -(t == 0 ? a0 : c[t - 1] * vp[t - 1]) * inv[t];
+                cq[t] = -c[t] * inv[t];
+                gl = gp[t];
+            }
+            if (t == m - 1) {
+                em = e[t];
+                cm = c[t];
+                am = t > 0 ? c[t - 1] : (T)0;
+            }
+        }
+        T g0 = gl;
+#pragma unroll
+        for (int t = LMAX - 1; t >= 0; --t)
+            if (t < m - 2) g0 = gp[t] + cq[t] * g0;
+        if (!active) g0 = 0;
+        const T gn = __shfl_down(g0, 1, 64);
+        T re = em - am * gl - cm * (lane + 1 < S ? gn : (T)0);
+        if (!active) re = 0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            if ((1 << k) >= S) break;
+            const T up = __shfl_up(re, 1 << k, 64), dn = __shfl_down(re, 1 << k, 64);
+            re += al[k] * up + ga[k] * dn;
+        }
+        const T X = re * piv;
+        T Xp = __shfl_up(X, 1, 64);
+        if (lane == 0) Xp = 0;
+        T y = X;
+#pragma unroll
+        for (int t = LMAX - 1; t >= 0; --t) {
+            if (t == m - 1) te[lo + t] = X;
+            if (t < m - 1) {
+                y = gp[t] + vp[t] * Xp + cq[t] * y;
+                te[lo + t] = y;
+            }
+        }
+    }
+};
+
+// The lane's rows [lo, lo + m) of G strips over S lanes.
+__device__ inline void red_lane(int G, int lane, int &S, int &lo, int &m)
+{
+    S = G < 64 ? G : 64;
+    lo = lane < S ? (int)(((long)lane * G) / S) : G;
+    m = (lane < S ? (int)(((long)(lane + 1) * G) / S) : G) - lo;
+}
+
 // LDS of the reduced-system phase: the r-line arrays (padded, LdsLines) and
 // the reduced data of `mt` modes, [mt][G] each for E1 and G0.
 template <typename T>
@@ -240,23 +348,41 @@ __host__ __device__ inline size_t strip_red_lds(int nr, int G, int mt)
 {
     return (3 * (size_t)(nr + nr / 32 + 1) + 2 * (size_t)mt * G) * sizeof(T);
 }
+// The same with the factored coefficients: the reduced data only.
+template <typename T>
+__host__ __device__ inline size_t strip_fac_lds(int G, int mt) { return 2 * (size_t)mt * G * sizeof(T); }
 
 // (nr here and in strip_solve2: G strips' rows, the padded ones included.)
 // Phase 2 (K2) part 1: stage the r-line arrays and the reduced data of modes
 // [l0, l0 + mt) into LDS (`base`); vector loads when the mt values of a
 // strip's row are 16-byte pieces.
 template <typename T, bool VEC>
+__device__ __forceinline__ void stage_red(const T *__restrict__ red_e, const T *__restrict__ red_g, int N, int G,
+                                          int l0, int mt, T *te);
+template <typename T, bool VEC>
+__device__ __forceinline__ void store_red(T *__restrict__ red_x, int N, int G, int l0, int mt, const T *te);
+
+template <typename T, bool VEC>
 __device__ __forceinline__ void strip_stage2(const T *__restrict__ red_e, const T *__restrict__ red_g,
                                              const Lines<T> &ln, int nr, int N, int G, int l0, int mt, T *base)
 {
     const int npad = nr + nr / 32 + 1;
-    T *lc = base, *ld = lc + npad, *lw = ld + npad, *te = lw + npad, *tg = te + mt * G;
+    T *lc = base, *ld = lc + npad, *lw = ld + npad;
     for (int i = threadIdx.x; i < nr; i += blockDim.x) {
         const int a = LdsLines<T>::at(i);
         lc[a] = ln.cb[i];
         ld[a] = ln.db[i];
         lw[a] = ln.rw[i];
     }
+    stage_red<T, VEC>(red_e, red_g, N, G, l0, mt, lw + npad);
+}
+
+// The reduced data alone, te [mt][G] then tg [mt][G].
+template <typename T, bool VEC>
+__device__ __forceinline__ void stage_red(const T *__restrict__ red_e, const T *__restrict__ red_g, int N, int G,
+                                          int l0, int mt, T *te)
+{
+    T *tg = te + mt * G;
     if constexpr (VEC) {
         constexpr int VW = 16 / (int)sizeof(T);
         typedef T V __attribute__((ext_vector_type(VW)));
@@ -331,6 +457,13 @@ __device__ __forceinline__ void strip_solve2(T *__restrict__ red_x, const Lines<
         for (int k = 0; k < LMAX; ++k)
             if (k < m) te[w * G + lo + k] = xs[k];
     }
+    store_red<T, VEC>(red_x, N, G, l0, mt, te);
+}
+
+// The solutions te [mt][G] to red_x, once every wave has put its own there.
+template <typename T, bool VEC>
+__device__ __forceinline__ void store_red(T *__restrict__ red_x, int N, int G, int l0, int mt, const T *te)
+{
     __syncthreads();
     if constexpr (VEC) {
         constexpr int VW = 16 / (int)sizeof(T);

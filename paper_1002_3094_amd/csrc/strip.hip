@@ -80,6 +80,147 @@ k_strip_reduced(const T *__restrict__ red_e, const T *__restrict__ red_g, T *__r
     strip_solve2<T, R, LMAX, VEC>(red_x, ln, nr, N, G, l0, MT, base);
 }
 
+// The same for strips of four rows with the factored coefficients, each wave's
+// factors on their way before the stop test.  Bound by its chain of latencies
+// (stop test, staging, the wave's solve); against recomputing the coefficients:
+// 8.2 -> 6.6 us at 1024^2 FP32, 6.8 -> 5.0 us at 512^2 FP32, 10.1 -> 6.9 us at
+// 1021 x 512 FP64, for 6 MB of factors read at 1024^2 FP32.
+template <typename T, int LMAX, int MT>
+__global__ void __launch_bounds__(64 * MT)
+k_strip_reduced_f(const T *__restrict__ red_e, const T *__restrict__ red_g, T *__restrict__ red_x,
+                  const T *__restrict__ fac, const T *__restrict__ cb, PcgState *st,
+                  const double *__restrict__ partials, TriGate g, int N, int G)
+{
+    __shared__ double red[RED_SLOTS];
+    extern __shared__ char smem_raw[];
+    T *te = reinterpret_cast<T *>(smem_raw);
+    const int l0 = xcd_swizzle(blockIdx.x, N / MT) * MT;
+    constexpr bool VEC = MT % (16 / (int)sizeof(T)) == 0;   // 16-byte staging loads
+    GatePre pre;
+    if (g.mode == 1) gate_issue(st, partials, g, pre);
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int S, lo, m;
+    red_lane(G, lane, S, lo, m);
+    RedFac<T, LMAX> f;
+    f.load(fac, l0 + w, LMAX, cb, lo, m, lane);
+    stage_red<T, VEC>(red_e, red_g, N, G, l0, MT, te);
+    if (g.mode != 0 && tridiag_gate(st, partials, g, red, blockIdx.x, g.mode == 1 ? &pre : nullptr) != ST_RUN)
+        return;
+    __syncthreads();
+    f.solve(te + w * G, te + (MT + w) * G, G, lo, m, S, lane);
+    store_red<T, VEC>(red_x, N, G, l0, MT, te);
+}
+
+// The factors (RedFac), one wave per mode, in FP64 from the r-line arrays of
+// precision T: the strips' preparatory solutions (strip_coefs), the reduced
+// rows, the elimination of each lane's rows and the cyclic reduction of
+// wave_tri, all without their right-hand sides.
+template <typename T, int LMAX>
+__global__ void __launch_bounds__(64)
+k_strip_factors(Lines<T> ln, T *__restrict__ fac, int G)
+{
+    constexpr int R = 4, n = R - 1;
+    const int l = blockIdx.x, lane = threadIdx.x;
+    int S, lo, m;
+    red_lane(G, lane, S, lo, m);
+    const bool active = lane < S;
+    const double lam = ln.lam[l];
+    double a[LMAX], b[LMAX], c[LMAX];
+    // strip s: its first row's response (v0, w0) to the interface rows on either
+    // side and its last interior row's (vL, wL)
+    auto coefs = [&](int s, double &vL, double &wL, double &v0, double &w0) {
+        const int i0 = s * R;
+        double cp[R], vp[R], cprev = 0, vprev = 0;
+#pragma unroll
+        for (int t = 0; t < n; ++t) {
+            const double L = t > 0 ? (double)ln.cb[i0 + t - 1] : 0.0;
+            const double inv = 1.0 / ((double)ln.db[i0 + t] + (double)ln.rw[i0 + t] * lam - L * cprev);
+            cprev = (double)ln.cb[i0 + t] * inv;
+            vprev = (t == 0 ? (s > 0 ? (double)ln.cb[i0 - 1] : 0.0) : L * vprev) * inv;
+            cp[t] = cprev;
+            vp[t] = vprev;
+        }
+        vL = v0 = vp[n - 1];
+        wL = w0 = cp[n - 1];
+#pragma unroll
+        for (int t = n - 2; t >= 0; --t) {
+            v0 = vp[t] + cp[t] * v0;
+            w0 = cp[t] * w0;
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < LMAX; ++k) {
+        a[k] = c[k] = 0;
+        b[k] = 1;
+        if (k < m) {
+            const int s = lo + k, j = s * R + n;
+            double vL, wL, v0, w0, vn = 0, wn = 0, x, y;
+            coefs(s, vL, wL, v0, w0);
+            const double cjm = ln.cb[j - 1], cj = s + 1 < G ? (double)ln.cb[j] : 0.0;
+            if (s + 1 < G) coefs(s + 1, x, y, vn, wn);
+            a[k] = -cjm * vL;
+            b[k] = (double)ln.db[j] + (double)ln.rw[j] * lam - cjm * wL - cj * vn;
+            c[k] = -cj * wn;
+        }
+    }
+    T *f = fac + (size_t)l * red_items(LMAX) * 64 + lane;
+    double vl = 0, wl = 0, v0 = 0, w0 = 1, vp[LMAX], cq[LMAX];
+#pragma unroll
+    for (int t = 0; t < LMAX; ++t) {
+        double inv = 0;
+        if (t < m - 1) {
+            inv = 1.0 / (t == 0 ? b[0] : b[t] + a[t] * cq[t - 1]);
+            vp[t] = -(t == 0 ? a[0] : a[t] * vp[t - 1]) * inv;
+            cq[t] = -c[t] * inv;
+            vl = vp[t];
+            wl = cq[t];
+        }
+        if (t < LMAX - 1) f[t * 64] = (T)inv;
+        f[(LMAX - 1 + t) * 64] = (T)c[t];
+    }
+    f += (2 * LMAX - 1) * 64;
+    f[0] = (T)a[0];
+    if (m >= 2) {
+        v0 = vl;
+        w0 = wl;
+#pragma unroll
+        for (int t = LMAX - 1; t >= 0; --t)
+            if (t < m - 2) {
+                v0 = vp[t] + cq[t] * v0;
+                w0 = cq[t] * w0;
+            }
+    }
+    if (!active) v0 = w0 = 0;
+    const double V0n = __shfl_down(v0, 1, 64), W0n = __shfl_down(w0, 1, 64);
+    double ra = 0, rb = 1, rc = 0;
+    if (active) {
+        double am = 0, bm = 0, cm = 0;
+#pragma unroll
+        for (int t = 0; t < LMAX; ++t)
+            if (t == m - 1) { am = a[t]; bm = b[t]; cm = c[t]; }
+        const bool next = lane + 1 < S;
+        ra = m >= 2 ? am * vl : am;
+        rb = bm + (m >= 2 ? am * wl : 0.0) + (next ? cm * V0n : 0.0);
+        rc = next ? cm * W0n : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        const int k = 1 << q;
+        const double am = __shfl_up(ra, k, 64), bm = __shfl_up(rb, k, 64), cm = __shfl_up(rc, k, 64);
+        const double ap = __shfl_down(ra, k, 64), bp = __shfl_down(rb, k, 64), cp = __shfl_down(rc, k, 64);
+        const bool hm = active && k < S && lane >= k, hp = active && k < S && lane + k < S;
+        const double al = hm ? -ra / bm : 0.0, ga = hp ? -rc / bp : 0.0;
+        if (active && k < S) {
+            rb += (hm ? al * cm : 0.0) + (hp ? ga * ap : 0.0);
+            ra = hm ? al * am : 0.0;
+            rc = hp ? ga * cp : 0.0;
+        }
+        f[(1 + q) * 64] = (T)al;
+        f[(7 + q) * 64] = (T)ga;
+    }
+    f[13 * 64] = (T)(active ? 1.0 / rb : 0.0);
+}
+
 template <typename T, int BC, int MODE, int R2, int R>
 __global__ void __launch_bounds__(64 * R)
 k_strip_inv(const T *__restrict__ fprime, const T *__restrict__ red_x, ZOut<T, MODE> *__restrict__ zout,
@@ -113,6 +254,13 @@ template <>
 const float2 *pt_of<float>(const Operator &op) { return op.pt32; }
 template <>
 const double2 *pt_of<double>(const Operator &op) { return op.pt64; }
+
+template <typename T>
+T *fac_of(const Operator &op);
+template <>
+float *fac_of<float>(const Operator &op) { return op.red_fac32; }
+template <>
+double *fac_of<double>(const Operator &op) { return op.red_fac64; }
 
 template <typename T>
 struct RedBufs {
@@ -191,6 +339,19 @@ void inv_r(const Operator &op, const ZinvArgs &a, hipStream_t s)
     AXI_CHECK_HIP(hipGetLastError());
 }
 
+template <typename T, int LM, int MT>
+void red_launch_f(const Operator &op, const TriGate &g, hipStream_t s)
+{
+    const RedBufs<T> rb = red_bufs<T>(op, 4);
+    const int G = strip_count(op.nr, 4);
+    const size_t shm = strip_fac_lds<T>(G, MT);
+    static bool lds_set = false;
+    allow_lds(reinterpret_cast<const void *>(&k_strip_reduced_f<T, LM, MT>), shm, lds_set);
+    hipLaunchKernelGGL((k_strip_reduced_f<T, LM, MT>), dim3(op.nz / MT), dim3(64 * MT), shm, s, rb.e, rb.g, rb.x,
+                       fac_of<T>(op), lines_of<T>(op).cb, g.state, op.partials, g, op.nz, G);
+    AXI_CHECK_HIP(hipGetLastError());
+}
+
 template <typename T, int R, int LM, int MT>
 void red_launch_mt(const Operator &op, const TriGate &g, hipStream_t s)
 {
@@ -216,6 +377,15 @@ void red_launch(const Operator &op, const TriGate &g, hipStream_t s)
 template <typename T, int R>
 void red_r(const Operator &op, const TriGate &g, hipStream_t s)
 {
+    if constexpr (R == 4) {   // the reduced data of red_mt modes always fit LDS
+        switch (red_rows(strip_count(op.nr, 4))) {
+        case 1: return red_launch_f<T, 1, red_mt<T>()>(op, g, s);
+        case 2: return red_launch_f<T, 2, red_mt<T>()>(op, g, s);
+        case 4: return red_launch_f<T, 4, red_mt<T>()>(op, g, s);
+        case 8: return red_launch_f<T, 8, red_mt<T>()>(op, g, s);
+        default: return red_launch_f<T, 16, red_mt<T>()>(op, g, s);
+        }
+    }
     const int per = (strip_count(op.nr, R) + 63) / 64;
     if (per <= 1) red_launch<T, R, 1>(op, g, s);
     else if (per <= 2) red_launch<T, R, 2>(op, g, s);
@@ -306,6 +476,33 @@ bool strip_usable(const Operator &op, int prec, int rows)
 {
     if (!op.strip_red) return false;
     return prec == AXIPCG_PREC_FP32 ? usable_t<float>(op, rows) : usable_t<double>(op, rows);
+}
+
+// The factors of the reduced systems (strips of four rows), for each precision
+// whose transforms the strips take.
+template <typename T>
+static void factors_t(const Operator &op, T **fac, hipStream_t s)
+{
+    if (strip_r2<T>(op.nz) == 0 || strip_count(op.nr, 4) > 1024) return;
+    const int G = strip_count(op.nr, 4), L = red_rows(G);
+    void *p = nullptr;
+    const hipError_t e = hipMalloc(&p, sizeof(T) * (size_t)op.nz * red_items(L) * 64);
+    if (e != hipSuccess) throw Error{AXIPCG_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e)};
+    *fac = static_cast<T *>(p);
+#define AXI_FAC(LM) hipLaunchKernelGGL((k_strip_factors<T, LM>), dim3(op.nz), dim3(64), 0, s, lines_of<T>(op), *fac, G)
+    if (L == 1) AXI_FAC(1);
+    else if (L == 2) AXI_FAC(2);
+    else if (L == 4) AXI_FAC(4);
+    else if (L == 8) AXI_FAC(8);
+    else AXI_FAC(16);
+#undef AXI_FAC
+    AXI_CHECK_HIP(hipGetLastError());
+}
+
+void strip_factors(Operator &op, hipStream_t s)
+{
+    factors_t<float>(op, &op.red_fac32, s);
+    factors_t<double>(op, &op.red_fac64, s);
 }
 
 // Reduced data for strips of 4 rows (the larger of the two heights' needs).

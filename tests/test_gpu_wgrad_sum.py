@@ -13,10 +13,18 @@ from tests.gpu_util import dev
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module")
+def ax():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1002_3094_amd import axipcg
+    axipcg.lib()
+    return axipcg
+
+
 @pytest.mark.parametrize("segments", [2, 7, 121, 128, 129, 263])
-def test_weight_gradient_over_segments(orc, segments):
+def test_weight_gradient_over_segments(ax, orc, segments):
     from oracle import nn as onn
-    from paper_1002_3094_amd import axipcg as ax
     nr, nz = segments, 64
     ex = synth.nn_example(nr, nz, seed=segments)
     q = np.full((nr, nz), 0.5)
