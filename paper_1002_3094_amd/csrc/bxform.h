@@ -96,12 +96,6 @@ struct BlockFft {
     }
 };
 
-// Has the value computed here: the compiler's code sinking moves LDS reads whose
-// results are first used in a later block down past the workgroup barriers in
-// between, where others already overwrite the buffer.
-template <typename T>
-__device__ __forceinline__ void in_register(T &v) { asm volatile("" : "+v"(v)); }
-
 // Spectra of one row (ROWS 1) or of two, both real, through one complex FFT
 // (the second row in the imaginary parts, zero unless `two`): v0, v1 hold the
 // thread's pairs (2 (t + j NT), + 1), s0, s1 receive modes t + e NT.  The

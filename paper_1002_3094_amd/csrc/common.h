@@ -345,6 +345,12 @@ __device__ inline double block_total(const double *__restrict__ parts, int n, do
     return s;
 }
 
+// Has the value computed here: the compiler's code sinking moves LDS reads whose
+// results are first used in a later block down past the workgroup barriers in
+// between, where others already overwrite the buffer.
+template <typename T>
+__device__ __forceinline__ void in_register(T &v) { asm volatile("" : "+v"(v)); }
+
 // Map a block index to a logical tile so that each XCD (blocks are dealt to
 // the 8 XCDs round-robin) works on one contiguous range of tiles.
 __device__ inline int xcd_swizzle(int b, int nb)

@@ -88,6 +88,12 @@ void strip_fwd(const Operator &op, int prec, int rows, const ZfwdArgs &a, hipStr
 void strip_reduced(const Operator &op, int prec, int rows, const TriGate &g, hipStream_t s);
 void strip_inv(const Operator &op, int prec, int rows, const ZinvArgs &a, hipStream_t s);
 
+// The whole PCG solve of a small grid in one launch of one workgroup
+// (tiny.hip); publishes its outcome to the host mirror.
+bool tiny_usable(const Operator &op);
+void tiny_pcg(const Operator &op, const double *b, double *x, double rtol2, int maxit, int prec, int flags,
+              unsigned seq, hipStream_t s);
+
 // z = B^{-1} r with three launches (forward, r-solves, inverse).
 void precond_apply_impl(const Operator &op, const double *r, double *z, int prec, hipStream_t s);
 

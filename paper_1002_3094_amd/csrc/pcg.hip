@@ -292,6 +292,36 @@ PcgState wait_progress(Operator &op, hipStream_t s, unsigned seq, int need)
     }
 }
 
+// Statistics and status of a PCG solve whose outcome the host has seen.
+int finish(Operator &op, const double *b, const double *x, const PcgState &h, unsigned flags, axipcg_stats *st,
+           hipStream_t s, bool sync_end)
+{
+    op.last_iters = h.iters;
+    if (op.prof_kernel >= 0) collect_profile(op, h.iters);
+    int status;
+    if (h.done == ST_CONV || h.done == ST_BZERO) status = AXIPCG_OK;
+    else if (h.done == ST_BREAK) status = AXIPCG_EBREAKDOWN;
+    else status = AXIPCG_ENOTCONV;
+    if (st) {
+        st->iters = h.iters;
+        st->status = status;
+        st->relres_rec = (h.bb > 0) ? std::sqrt(h.rr / h.bb) : 0.0;
+        st->relres_true = -1.0;
+        if (flags & AXIPCG_FLAG_TRUE_RESIDUAL) {
+            if (h.bb > 0) {
+                resid_impl(op, b, x, op.dscal, s);
+                AXI_CHECK_HIP(hipMemcpyAsync(op.scratch_host, op.dscal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+                AXI_CHECK_HIP(hipStreamSynchronize(s));
+                st->relres_true = std::sqrt(op.scratch_host[0] / op.scratch_host[1]);
+            } else {
+                st->relres_true = 0.0;
+            }
+        }
+    }
+    if (sync_end) AXI_CHECK_HIP(hipStreamSynchronize(s));
+    return status;
+}
+
 int solve_impl(Operator &op, const double *b, double *x, double rtol, int maxit, int prec, unsigned flags,
                axipcg_stats *st, hipStream_t s, bool sync_end)
 {
@@ -303,6 +333,14 @@ int solve_impl(Operator &op, const double *b, double *x, double rtol, int maxit,
     c.one = op.fused_enabled && prec == AXIPCG_PREC_FP32 && !c.pr && pfused_plan(op, AXIPCG_FUSED_PCG) &&
             op.pf[AXIPCG_FUSED_PCG].G == c.n_tr;
     op.prof_used = 0;
+    PcgState h{};
+    // small grids in one launch (without the Polak-Ribiere form and the
+    // per-kernel timing, which belong to the launches)
+    if (!c.pr && op.prof_kernel < 0 && tiny_usable(op)) {
+        tiny_pcg(op, b, x, rtol * rtol, maxit, prec, (int)flags, c.seq, s);
+        h = wait_progress(op, s, c.seq, -1);
+        return finish(op, b, x, h, flags, st, s, sync_end);
+    }
     // start: r = b - A x; z = B^{-1} r (the r-solve launch runs the start test)
     const unsigned gi = row_blocks(op.nr);
     hipLaunchKernelGGL(k_pcg_init, dim3(gi), dim3(256), 0, s, b, x, op.r, op.D, op.CR, op.CZ, op.nr, op.nz,
@@ -340,7 +378,6 @@ int solve_impl(Operator &op, const double *b, double *x, double rtol, int maxit,
     int launched = 0;
     int parity = 0;
     int chunk = op.last_iters > 0 ? op.last_iters : 4;
-    PcgState h{};
     for (;;) {
         if (chunk > maxit - launched) chunk = maxit - launched;
         c.report_it = launched + chunk - 1;
@@ -353,30 +390,7 @@ int solve_impl(Operator &op, const double *b, double *x, double rtol, int maxit,
         if (h.done != ST_RUN || launched >= maxit) break;
         chunk = 2;
     }
-    op.last_iters = h.iters;
-    if (op.prof_kernel >= 0) collect_profile(op, h.iters);
-    int status;
-    if (h.done == ST_CONV || h.done == ST_BZERO) status = AXIPCG_OK;
-    else if (h.done == ST_BREAK) status = AXIPCG_EBREAKDOWN;
-    else status = AXIPCG_ENOTCONV;
-    if (st) {
-        st->iters = h.iters;
-        st->status = status;
-        st->relres_rec = (h.bb > 0) ? std::sqrt(h.rr / h.bb) : 0.0;
-        st->relres_true = -1.0;
-        if (flags & AXIPCG_FLAG_TRUE_RESIDUAL) {
-            if (h.bb > 0) {
-                resid_impl(op, b, x, op.dscal, s);
-                AXI_CHECK_HIP(hipMemcpyAsync(op.scratch_host, op.dscal, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-                AXI_CHECK_HIP(hipStreamSynchronize(s));
-                st->relres_true = std::sqrt(op.scratch_host[0] / op.scratch_host[1]);
-            } else {
-                st->relres_true = 0.0;
-            }
-        }
-    }
-    if (sync_end) AXI_CHECK_HIP(hipStreamSynchronize(s));
-    return status;
+    return finish(op, b, x, h, flags, st, s, sync_end);
 }
 
 // Chebyshev form of eq. (8): start r = b - A x, z = B^{-1} r (start test),
