@@ -152,7 +152,9 @@ int axipcg_precond_apply(axipcg_op_t op, const double *r, double *z, int prec, v
  * Standalone FP32 applies of rows of length 2048 use strips of 8 rows where 8
  * divides nr (faster there), and the solves' FP32 launches at that length use strips of
  * 4 whatever the height (their in-loop kernels need the registers of 4-wave
- * workgroups); strips_info reports the solves' strips.
+ * workgroups).  Until set_strips or set_fused is called for the handle, FP32
+ * solves of at most 512 rows of length 2048 run the per-mode r-solve (faster
+ * there).  strips_info reports the solves' strips.
  * strips_info reports whether the strip form is used for `prec` and its
  * strip count (host pointers, may be NULL). */
 int axipcg_op_set_strips(axipcg_op_t op, int enable);

@@ -152,6 +152,7 @@ struct Operator {
     float *red_fac32 = nullptr;    // factors of the reduced systems (strip.h, RedFac), where the
     double *red_fac64 = nullptr;   // strips' transforms cover nz in that precision
     int strip_rows = 4;   // strip height (4 or 8), 0 = the per-mode r-solve instead
+    bool strips_set = false;   // strip_rows was chosen by the caller
 
     // single-launch preconditioner (pfused.hip): plans [standalone, PCG]
     PfPlan pf[2];

@@ -196,7 +196,8 @@ void zfwd_ttr(const Operator &op, const ZfwdArgs &a, hipStream_t s)
 }
 
 // Rows per workgroup of the one-wave transforms for length N, 0 when N has
-// no one-wave plan (then the block-wide Stockham kernels run).
+// no one-wave plan (then block-wide kernels run, as they do for unbatched rows of
+// 2048 outside the strips).
 template <typename T>
 int wave_plan_rows(int N)
 {
@@ -249,16 +250,11 @@ void zfwd_t(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     case 256: return zfwd_wave<T, BC, 2>(op, a, s);
     case 512: return zfwd_wave<T, BC, 4>(op, a, s);
     case 1024: return zfwd_wave<T, BC, 8>(op, a, s);
-    case 2048:
-        if constexpr (sizeof(T) == 4) return zfwd_wave<T, BC, 16>(op, a, s);
-        break;
     default: break;
     }
     const int rows = transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32);
     if (block8(op.nz)) {
-        if constexpr (sizeof(T) == 8) {
-            if (op.nz == 2048) return rows == 2 ? zfwd8_t<T, BC, 2048, 2>(op, a, s) : zfwd8_t<T, BC, 2048, 1>(op, a, s);
-        }
+        if (op.nz == 2048) return rows == 2 ? zfwd8_t<T, BC, 2048, 2>(op, a, s) : zfwd8_t<T, BC, 2048, 1>(op, a, s);
         return rows == 2 ? zfwd8_t<T, BC, 4096, 2>(op, a, s) : zfwd8_t<T, BC, 4096, 1>(op, a, s);
     }
     // rows of up to 128 points, whose twiddles fit LDS
@@ -371,16 +367,11 @@ void zinv_t(const Operator &op, const ZinvArgs &a, hipStream_t s)
     case 256: return zinv_wave<T, BC, 2>(op, a, s);
     case 512: return zinv_wave<T, BC, 4>(op, a, s);
     case 1024: return zinv_wave<T, BC, 8>(op, a, s);
-    case 2048:
-        if constexpr (sizeof(T) == 4) return zinv_wave<T, BC, 16>(op, a, s);
-        break;
     default: break;
     }
     const int rows = transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32);
     if (block8(op.nz)) {
-        if constexpr (sizeof(T) == 8) {
-            if (op.nz == 2048) return rows == 2 ? zinv8_t<T, BC, 2048, 2>(op, a, s) : zinv8_t<T, BC, 2048, 1>(op, a, s);
-        }
+        if (op.nz == 2048) return rows == 2 ? zinv8_t<T, BC, 2048, 2>(op, a, s) : zinv8_t<T, BC, 2048, 1>(op, a, s);
         return rows == 2 ? zinv8_t<T, BC, 4096, 2>(op, a, s) : zinv8_t<T, BC, 4096, 1>(op, a, s);
     }
     if constexpr (sizeof(T) == 8) {
@@ -454,12 +445,26 @@ void tridiag_t(const Operator &op, const TriGate &gate, hipStream_t s)
 
 }  // namespace
 
-// Strip height of the solves' launches: the handle's, except that 8-row
-// strips at FP32 rows of 2048 (whose PCG-form kernels would spill registers
-// in 8-wave workgroups) run as 4-row strips.
-int strip_solve_rows(const Operator &op, int prec)
+// Strip height of the standalone applies and of the solves' launches: the
+// handle's, except that 8-row strips at FP32 rows of 2048 (whose PCG-form kernels
+// would spill registers in 8-wave workgroups) run as 4-row strips.
+static int strip_handle_rows(const Operator &op, int prec)
 {
     return (op.strip_rows == 8 && prec == AXIPCG_PREC_FP32 && op.nz == 2048) ? 4 : op.strip_rows;
+}
+
+// The solves leave strips for block-wide transforms and the per-mode r-solve
+// (0 returned) at up to 512 FP32 rows of 2048 points, unless the handle's strips
+// were set or its single launches, which are strips, are on: the strips' one-wave
+// transforms (32 points a lane) then occupy half of the 1024 SIMDs or fewer, one
+// wave each, and the r-solve's lines are short.  PCG solves, strips and block-wide
+// (us): 48 rows 1001 and 686, 256 rows 1186 and 864, 512 rows 1360 and 1205, 777
+// rows 1644 and 1696, 1024 rows 1843 and 1846; Chebyshev solves of 512 rows 1502
+// and 1315, of 777 1880 and 2012.
+int strip_solve_rows(const Operator &op, int prec)
+{
+    if (prec == AXIPCG_PREC_FP32 && op.nz == 2048 && op.nr <= 512 && !op.strips_set && !op.fused_enabled) return 0;
+    return strip_handle_rows(op, prec);
 }
 
 int transform_blocks(const Operator &op, int prec)
@@ -467,7 +472,7 @@ int transform_blocks(const Operator &op, int prec)
     const int sr = strip_solve_rows(op, prec);
     if (strip_usable(op, prec, sr)) return (op.nr + sr - 1) / sr;
     const int wr = (prec == AXIPCG_PREC_FP32) ? wave_plan_rows<float>(op.nz) : wave_plan_rows<double>(op.nz);
-    if (wr > 0) return (op.nr + wr - 1) / wr;
+    if (wr > 0 && !block8(op.nz)) return (op.nr + wr - 1) / wr;
     const int rows = transform_rows(op.nr, op.nz, prec);
     return (op.nr + rows - 1) / rows;
 }
@@ -656,11 +661,10 @@ void launch_tridiag(const Operator &op, int prec, const TriGate &g, hipStream_t 
 
 // Standalone applies of FP32 rows of length 2048 use strips of 8 rows when
 // strips are on (their transform kernels fit the registers of 8-wave
-// workgroups without the PCG vectors, and the reduced system halves); the
-// solves keep strip_solve_rows.
+// workgroups without the PCG vectors, and the reduced system halves).
 void precond_apply_impl(const Operator &op, const double *r, double *z, int prec, hipStream_t s)
 {
-    int rows = strip_solve_rows(op, prec);
+    int rows = strip_handle_rows(op, prec);
     if (rows == 4 && prec == AXIPCG_PREC_FP32 && op.nz == 2048 && op.nr % 8 == 0 && strip_usable(op, prec, 8)) rows = 8;
     if (rows > 0 && strip_usable(op, prec, rows)) {
         ZfwdArgs fa;

@@ -516,6 +516,7 @@ int axipcg_op_set_strips(axipcg_op_t h, int enable)
         AXI_REQUIRE(enable == 0 || enable == 1 || enable == 4 || enable == 8,
                     "strip height must be 0 (off), 1 (default), 4 or 8");
         op->strip_rows = enable == 1 ? 4 : enable;
+        op->strips_set = true;
         return AXIPCG_OK;
     });
 }
