@@ -38,14 +38,14 @@ inline unsigned row_blocks(int nr) { return (unsigned)(nr < MAX_PARTIALS ? nr : 
 template <typename ZT, bool PR>
 constexpr int spmv_waves() { return (sizeof(ZT) == 4 && !PR) ? 4 : 3; }
 
-template <typename ZT, bool PR, int RW>
+template <typename ZT, bool PR, int RW, bool FOLD>
 __global__ void __launch_bounds__(SPMV_CHUNK / 2, (spmv_waves<ZT, PR>()))
 k_pcg_spmv(const ZT *__restrict__ z, const double *__restrict__ pold, double *__restrict__ pnew,
            double *__restrict__ q, double *__restrict__ x, const double *__restrict__ D,
            const double *__restrict__ CR, const double *__restrict__ CZ, int nr, int nz, PcgState *st,
            double *__restrict__ partials, int n_rz)
 {
-    spmv_tiles<ZT, PR, RW, SPMV_CHUNK>(z, pold, pnew, q, x, D, CR, CZ, nr, nz, st, partials, n_rz, blockIdx.x, gridDim.x);
+    spmv_tiles<ZT, PR, RW, SPMV_CHUNK, FOLD>(z, pold, pnew, q, x, D, CR, CZ, nr, nz, st, partials, n_rz, blockIdx.x, gridDim.x);
 }
 
 // Rows per SpMV tile: 16 when that still leaves 1024 tiles or more (long
@@ -57,9 +57,16 @@ int spmv_rows(int nr, int nz)
     return ((long)(nr / 16) * nc >= 1024) ? 16 : 2;
 }
 
+// Tiles to a workgroup of the two-row form, 1 but for short rows.
+int spmv_stack(int nr, int nz)
+{
+    const int f = spmv_rows(nr, nz) == 2 ? spmv_fold(nr, nz, SPMV_CHUNK) : 1;
+    return f > 1 ? f : 1;
+}
+
 unsigned spmv_blocks(int nr, int nz)
 {
-    const int rw = spmv_rows(nr, nz);
+    const int rw = spmv_rows(nr, nz) * spmv_stack(nr, nz);
     const long tiles = (long)((nr + rw - 1) / rw) * ((nz + SPMV_CHUNK - 1) / SPMV_CHUNK);
     return (unsigned)(tiles < MAX_PARTIALS ? tiles : MAX_PARTIALS);
 }
@@ -175,22 +182,24 @@ void launch_iteration(const SolveCtx &c, int parity, int iter)
     const unsigned gs = spmv_blocks(op.nr, op.nz);
     {
         ProfScope ps(op, c.s, AXIPCG_KERNEL_SPMV, iter, true);
-#define AXI_SPMV(ZT, PRV, RWV)                                                                                       \
-    hipExtLaunchKernelGGL((k_pcg_spmv<ZT, PRV, RWV>), dim3(gs), dim3(SPMV_CHUNK / 2), 0, c.s, ps.start(), ps.stop(), 0, \
-                          (const ZT *)op.z, pold, pnew, op.q, c.x, op.D, op.CR, op.CZ, op.nr, op.nz, op.state,       \
-                          op.partials, c.n_tr)
-#define AXI_SPMV_Z(PRV, RWV)                                    \
-    do {                                                        \
-        if (c.prec == AXIPCG_PREC_FP32) AXI_SPMV(float, PRV, RWV); \
-        else AXI_SPMV(double, PRV, RWV);                        \
+#define AXI_SPMV(ZT, PRV, RWV, FV)                                                                                   \
+    hipExtLaunchKernelGGL((k_pcg_spmv<ZT, PRV, RWV, FV>), dim3(gs), dim3(SPMV_CHUNK / 2), 0, c.s, ps.start(),         \
+                          ps.stop(), 0, (const ZT *)op.z, pold, pnew, op.q, c.x, op.D, op.CR, op.CZ, op.nr, op.nz,   \
+                          op.state, op.partials, c.n_tr)
+#define AXI_SPMV_Z(PRV, RWV, FV)                                    \
+    do {                                                            \
+        if (c.prec == AXIPCG_PREC_FP32) AXI_SPMV(float, PRV, RWV, FV); \
+        else AXI_SPMV(double, PRV, RWV, FV);                        \
     } while (0)
-        const bool long_tiles = spmv_rows(op.nr, op.nz) == 16;
+        const bool long_tiles = spmv_rows(op.nr, op.nz) == 16, stacked = spmv_stack(op.nr, op.nz) > 1;
         if (c.pr) {
-            if (long_tiles) AXI_SPMV_Z(true, 16);
-            else AXI_SPMV_Z(true, 2);
+            if (long_tiles) AXI_SPMV_Z(true, 16, false);
+            else if (stacked) AXI_SPMV_Z(true, 2, true);
+            else AXI_SPMV_Z(true, 2, false);
         } else {
-            if (long_tiles) AXI_SPMV_Z(false, 16);
-            else AXI_SPMV_Z(false, 2);
+            if (long_tiles) AXI_SPMV_Z(false, 16, false);
+            else if (stacked) AXI_SPMV_Z(false, 2, true);
+            else AXI_SPMV_Z(false, 2, false);
         }
 #undef AXI_SPMV_Z
 #undef AXI_SPMV

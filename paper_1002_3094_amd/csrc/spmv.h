@@ -90,13 +90,25 @@ __device__ inline Pair stencil2(const double *__restrict__ v, const double *__re
 constexpr int SPMV_CHUNK = 256;
 constexpr int BATCH_ONE_CHUNK = 512;
 
+// Rows shorter than CHUNK: FOLD deals a workgroup's threads to several tiles, one
+// above the other, where all but nz / 2 threads would idle; as many as fit and
+// leave 256 workgroups of two rows a tile, below which the idle threads cost less
+// than the idle CUs.  PCG solves, plain and stacked (us): 4000 x 32 FP64 2001 and
+// 1811, FP32 1845 and 1728, 4000 x 128 FP64 2501 and 2375; 592 x 32 FP32 without
+// the row limit 675 and 717.
+__host__ __device__ inline int spmv_fold(int nr, int nz, int chunk)
+{
+    const int fit = chunk / nz, keep = nr / 512;
+    return fit < keep ? fit : keep;   // 0 and 1: not folded
+}
+
 // z comes in the preconditioner's own type ZT: an FP32 preconditioner's z
 // holds float values, so as floats it is the same vector in half the bytes.
 // With the x update here and z so, an FP32 iteration moves 114 bytes a point
 // instead of 130: 541 against 594 us at 4096^2 (SpMV 195 -> 222, forward
 // 207 -> 150, inverse 119 -> 105), 25.5 against 26.9 us for SpMV and forward
 // at 1024^2, 7.5 against 8.5 ms for 24 uneven problems.
-template <typename ZT, bool PR, int RW, int CHUNK>
+template <typename ZT, bool PR, int RW, int CHUNK, bool FOLD = false>
 __device__ __forceinline__ void spmv_tiles(const ZT *__restrict__ z, const double *__restrict__ pold,
                                            double *__restrict__ pnew, double *__restrict__ q, double *__restrict__ x,
                                            const double *__restrict__ D, const double *__restrict__ CR,
@@ -107,8 +119,11 @@ __device__ __forceinline__ void spmv_tiles(const ZT *__restrict__ z, const doubl
     double acc = 0.0, beta = 0.0, aprev = 0.0;
     bool have_beta = false;
     int k_it = 0;
-    const int nb = (nr + RW - 1) / RW, nc = (nz + CHUNK - 1) / CHUNK;
+    const int fold = FOLD ? spmv_fold(nr, nz, CHUNK) : 1, high = RW * fold;
+    const int nb = (nr + high - 1) / high, nc = (nz + CHUNK - 1) / CHUNK;
     const int lane = threadIdx.x & 63;
+    // this thread's tile within the workgroup
+    const int sub = FOLD ? 2 * (int)threadIdx.x / nz : 0;
     // the first round of the r.z partials, issued ahead of the first tile's
     // rows so that the two reads are in flight together (not in the
     // Polak-Ribiere form, whose second sum would cost it a wave per SIMD)
@@ -116,9 +131,9 @@ __device__ __forceinline__ void spmv_tiles(const ZT *__restrict__ z, const doubl
     if constexpr (!PR) total_issue(partials + SLOT_RZ * MAX_PARTIALS, n_rz, rz_pre);
     for (int t = vb; t < nb * nc; t += vnb) {
         const int item = xcd_swizzle(t, nb * nc);
-        const int i0 = RW * (item / nc);
-        const int k = (item % nc) * CHUNK + 2 * (int)threadIdx.x;
-        const bool in = k < nz;
+        const int first = high * (item / nc), i0 = first + RW * sub;
+        const int k = (item % nc) * CHUNK + 2 * (int)threadIdx.x - sub * nz;
+        const bool in = k < nz && (!FOLD || (sub < fold && i0 < nr));
         const bool le = lane == 0 && in && k > 0, re = lane == 63 && in && k + 2 < nz;
         // what row i needs beyond the window: z, p_old of row i + 1, and its
         // own coefficients, x and (at the wave's edges) outer neighbours
@@ -164,7 +179,7 @@ __device__ __forceinline__ void spmv_tiles(const ZT *__restrict__ z, const doubl
 #pragma unroll
         for (int rr = 0; rr < RW; ++rr) {
             const int i = i0 + rr;
-            if (i >= nr) break;
+            if (first + rr >= nr) break;   // (the workgroup's uppermost tile: all threads alike)
             const bool up = i + 1 < nr;
             const size_t e = (size_t)i * nz + k;
             if (rr + 1 < RW) load(i + 1, nxt);
@@ -220,7 +235,7 @@ __device__ __forceinline__ void spmv_tiles(const ZT *__restrict__ z, const doubl
                 if (vb == 0 && threadIdx.x == 0) st->rho[k_it & 1] = rho;
                 have_beta = true;
             }
-            if (in) {
+            if (in && (!FOLD || i < nr)) {
                 double2 pn, qn;
                 pn.x = (k_it > 0) ? (double)zw[1].a + beta * pw[1].a : (double)zw[1].a;
                 pn.y = (k_it > 0) ? (double)zw[1].b + beta * pw[1].b : (double)zw[1].b;
