@@ -45,10 +45,10 @@ HBM_PEAK_GBS = 8000.0
 # Algorithmic bytes per grid point of each PCG kernel class with the FP32
 # preconditioner (FP64 = 8 B, FP32 = 4 B per value).
 BYTES_PER_POINT = {   # one PCG iteration, FP32 preconditioner in 4-row strips
-    "spmv": 56,      # read z, p_old, D, CR, CZ; write p, q
-    "zfwd": 53,      # read x, r, p, q; write x, r, 3/4 of f' (f32), E1 and G0 (2 f32 per strip and mode)
+    "spmv": 68,      # read z (f32), p_old, x, D, CR, CZ; write x, p, q
+    "zfwd": 29,      # read r, q; write r, 3/4 of f' (f32), E1 and G0 (2 f32 per strip and mode)
     "tridiag": 3,    # read E1, G0; write X (f32 per strip and mode)
-    "zinv": 21,      # read 3/4 of f', X of the strip and the one before, r; write z
+    "zinv": 17,      # read 3/4 of f', X of the strip and the one before, r; write z (f32)
 }
 PRECOND_BYTES_PER_POINT = 32  # r (8) -> spectral (4+4) -> spectral (4+4) -> z (8)
 PRECOND_BYTES_PER_POINT_FP64 = 48  # r (8) -> spectral (8+8) -> spectral (8+8) -> z (8)

@@ -495,8 +495,8 @@ int axipcg_series_run_alpha(axipcg_op_t op, int m0, int count, int alpha, const 
  * and clears them if reset. */
 enum {
     AXIPCG_KERNEL_NONE = -1,
-    AXIPCG_KERNEL_SPMV = 0,    /* p update, q = A p, p.q           */
-    AXIPCG_KERNEL_ZFWD = 1,    /* x, r update, ||r||^2, transform  */
+    AXIPCG_KERNEL_SPMV = 0,    /* x, p update, q = A p, p.q        */
+    AXIPCG_KERNEL_ZFWD = 1,    /* r update, ||r||^2, transform     */
     AXIPCG_KERNEL_TRIDIAG = 2, /* r-solves, one per z-mode         */
     AXIPCG_KERNEL_ZINV = 3     /* inverse transform, r.z           */
 };
