@@ -129,7 +129,7 @@ def source_sha():
     hdr = open(os.path.join(csrc, "spmv.h")).read()
     h.update(hdr[hdr.index("struct Pair {"):hdr.index("// Chebyshev step of eq. (8) in increment form")].encode())
     pcg = open(os.path.join(csrc, "pcg.hip")).read()
-    h.update(pcg[pcg.index("template <bool PR, int RW>\n__global__"):pcg.index("// Chebyshev step of eq. (8)")].encode())
+    h.update(pcg[pcg.index("// Waves per SIMD the SpMV is compiled for"):pcg.index("// Chebyshev step of eq. (8)")].encode())
     com = open(os.path.join(csrc, "common.h")).read()
     for start in ("struct PcgState {", "enum Slot {", "constexpr int MAX_PARTIALS",
                   "__device__ inline double block_sum(", "struct TotalLoads {", "__device__ inline void total_issue(",
