@@ -55,11 +55,11 @@ void launch_tridiag(const Operator &op, int prec, const TriGate &g, hipStream_t 
 //  (mode 4: d = tau z), skipped once the stop test has fired.
 // The x update of a solve's last iteration `iter` (the earlier ones' are the
 // SpMV's): x += alpha p, done by the mode-1 inverse launch that finds the solve
-// stopped in its own iteration.
+// stopped in its own iteration.  Left at its defaults it asks for nothing.
 struct XFin {
     double *x = nullptr;
     const double *p = nullptr;
-    int iter = 0;
+    int iter = -1;
 };
 struct ZinvArgs {
     void *zout = nullptr;

@@ -212,8 +212,9 @@ zfwd_w_body(const double *__restrict__ rin, double *__restrict__ r, const double
 
 // x += alpha p over [base, base + n) (n even) by threads tid < nthr, when the
 // solve stopped in iteration fin.iter: forward ran (cur), with its step length.
-__device__ inline void x_finish(const XFin &fin, const PcgState *st, size_t base, int n, int tid, int nthr)
+__host__ __device__ inline void x_finish(const XFin &fin, const PcgState *st, size_t base, int n, int tid, int nthr)
 {
+    if (!fin.x) return;
     const double alpha = st->step.alpha;
     if (st->step.cur != fin.iter || alpha == 0.0) return;
     for (int k = 2 * tid; k < n; k += 2 * nthr) {
