@@ -166,13 +166,14 @@ int axipcg_op_strips_info(axipcg_op_t op, int prec, int *active, int *strips);
  * between the phases (only three values per strip and mode cross
  * workgroups), for FP32.  set_fused(op, 1) enables it for the handle's
  * standalone FP32 applies (strips of 8 rows for nz = 2048, else 4) and for
- * the iterations of its FP32 PCG solves (strips of 4; the x, r update, the
+ * the iterations of its FP32 PCG solves (strips of 4; the r update, the
  * stop test and the r.z partials in the same launch, after the SpMV), where
  * every strip's workgroup fits the chip at once and nz is 256..2048; the
  * three launches run otherwise.  Barriers are numbered from a per-handle
  * launch counter, and every wait is bounded: a barrier that gives up fills
- * the strip's output with NaN, marks a PCG solve broken down and sets the
- * handle's error word.  fused_info(op, kind, ...) reports for kind
+ * the strip's output with NaN, marks a PCG solve broken down (x then holds the
+ * whole iterate of the step it gave up in, which the statistics may not count)
+ * and sets the handle's error word.  fused_info(op, kind, ...) reports for kind
  * AXIPCG_FUSED_APPLY (0) or AXIPCG_FUSED_PCG (1) whether the single launch
  * is used and its strip count, and (synchronising the device) whether a
  * barrier ever gave up (host pointers, may be NULL). */

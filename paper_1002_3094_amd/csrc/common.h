@@ -56,7 +56,8 @@ struct PcgState {
     int maxit;
     int flags;
     struct Step {    // of the forward kernel, written as one piece
-        double alpha;   // step length of iteration `cur` (0 at the start)
+        double alpha;   // step length of iteration `cur` (0 at the start, and after a breakdown
+                        // found by the one-wave transforms: nothing left to add to x)
         int cur;        // iteration being processed
         int pad;
     } step;

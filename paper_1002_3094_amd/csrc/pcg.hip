@@ -11,7 +11,8 @@
 //               z-transform of r
 //   3. r-solve: ||r||^2 -> stop test (sets `done`); r-tridiagonal solves
 //   4. inverse: inverse z-transform -> z, r.z partials; once the stop test has
-//               fired, x += alpha_k p instead
+//               fired, x += alpha_k p instead (after single launches, a launch
+//               of its own does that)
 // After the stop test fires, the remaining launches of the chunk return at
 // once.  The host follows the solve through a progress record that the stop
 // test publishes to pinned host memory (HostMirror), normally once per solve.
@@ -24,6 +25,7 @@
 
 #include "kernels.h"
 #include "spmv.h"
+#include "wxform.h"
 
 namespace axipcg {
 
@@ -123,6 +125,17 @@ __global__ void k_zero_if_b_zero(double *__restrict__ x, size_t n, const PcgStat
     if (st->done != ST_BZERO) return;
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x)
         x[e] = 0.0;
+}
+
+// The last x update of a solve whose iterations were single launches (the
+// others' inverse launches do it): the step whose forward part ran last, if no
+// SpMV came after it.
+__global__ void __launch_bounds__(256)
+k_pcg_last_x(double *__restrict__ x, const double *__restrict__ p0, const double *__restrict__ p1, int n,
+             const PcgState *st)
+{
+    const int k = st->step.cur;
+    x_finish(XFin{x, (k & 1) ? p0 : p1, k}, st, 0, n, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
 struct SolveCtx {
@@ -398,6 +411,10 @@ int solve_impl(Operator &op, const double *b, double *x, double rtol, int maxit,
         h = wait_progress(op, s, c.seq, launched >= maxit ? -1 : c.report_it + 1);
         if (h.done != ST_RUN || launched >= maxit) break;
         chunk = 2;
+    }
+    if (c.one) {
+        hipLaunchKernelGGL(k_pcg_last_x, dim3(pointwise_blocks(n)), dim3(256), 0, s, x, op.p0, op.p1, (int)n, op.state);
+        AXI_CHECK_HIP(hipGetLastError());
     }
     return finish(op, b, x, h, flags, st, s, sync_end);
 }

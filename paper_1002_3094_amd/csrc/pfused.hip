@@ -23,6 +23,9 @@
 // counter (2 epoch + 1 and 2 epoch + 2).  A barrier that does not complete
 // within the spin limit sets the error word, fills the strip's output with
 // NaN and (in PCG mode) marks the solve broken down, and the kernel returns.
+// Workgroups may then disagree on whether the step was the last, so none of them
+// touches x here: the step's x += alpha p is the next SpMV's, or after the last
+// step a launch of its own (pcg.hip).
 #include "gridbar.h"
 #include "strip.h"
 
@@ -42,7 +45,6 @@ struct OneArgs {
     T *red_e, *red_g, *red_x;
     TriGate g;             // phase 2: stop test (mode 1) or none (mode 0)
     void *zout;            // phase 3
-    XFin fin;
     const typename vec2_of<T>::type *tw, *pt;
     Lines<T> ln;
     const T *fac;
@@ -82,10 +84,7 @@ __global__ void __launch_bounds__(64 * R) k_strip_one(OneArgs<T> A)
                                          A.red_g, A.tw, A.pt, A.ln, A.nr, s, tile))
         return;
     if (!grid_sync(A.bar, A.G, 2u * A.epoch + 1u, &flag)) return fail();
-    if (PCG && tridiag_gate(A.st, A.partials, A.g, red, s) != ST_RUN) {
-        x_finish(A.fin, A.st, (size_t)s * R * N, R * N, threadIdx.x, blockDim.x);
-        return;
-    }
+    if (PCG && tridiag_gate(A.st, A.partials, A.g, red, s) != ST_RUN) return;
     const int l0 = s * A.mpw, cnt = N - l0 < A.mpw ? N - l0 : A.mpw;
     if (cnt > 0 && R == 4) {
         // the factored systems, in the operations of the three-launch form
@@ -210,7 +209,6 @@ void pfused_pcg_step(Operator &op, const ZfwdArgs &fa, const TriGate &g, const Z
     const PfPlan &pl = op.pf[1];
     OneArgs<float> a = one_args(op, pl);
     a.r = fa.r;
-    a.fin = ia.fin;
     a.q = fa.q;
     a.st = fa.state;
     a.partials = op.partials;

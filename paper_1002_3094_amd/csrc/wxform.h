@@ -121,7 +121,10 @@ zfwd_w_body(const double *__restrict__ rin, double *__restrict__ r, const double
         const double rho_slot[2] = {st->rho[0], st->rho[1]};
         const double pq = block_total(partials + SLOT_PQ * MAX_PARTIALS, n_pq, red);
         if (!(pq > 0.0) || !(pq < 1e308)) {
-            if (blk == 0 && threadIdx.x == 0) st->done = ST_BREAK;
+            if (blk == 0 && threadIdx.x == 0) {
+                st->done = ST_BREAK;
+                st->step.alpha = 0.0;   // the last step's is in x since this iteration's SpMV
+            }
             return false;
         }
         alpha = rho_slot[k_it & 1] / pq;

@@ -1,31 +1,56 @@
-"""Compiles pieces of the library's HIP sources for the host alone and runs them
-here: what a kernel decides, or what a launcher asks of the HIP runtime, can be
-checked without a GPU.
+"""Runs the library's own host code, and device code that compiles for the host,
+without a GPU: what a kernel decides, which launches a call makes and what it asks
+of the runtime.
 
-`run` builds one program out of a driver text and, optionally, sources of the
-library; with sources, the HIP runtime is a small fake of the test's own, whose
-calls the driver sees (device memory is host memory, launches do nothing)."""
+`run` compiles a driver program for the host alone and returns what it prints; a
+crash or a non-zero exit fails the test.  With `library`, every source of the
+library is linked in, host code only, over the runtime of _fake_hip.h."""
+import glob
 import os
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(ROOT, "paper_1002_3094_amd", "csrc")
+FLAGS = ["--offload-arch=gfx950", "--cuda-host-only", "-x", "hip", "-O0", "-std=c++17", "-fPIC", "-w",
+         "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", HERE]
 
 
-def run(tmp_path, driver, sources=()):
-    """Output of the program; a crash or a non-zero exit fails the test."""
+def _compile(src, obj):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    text = os.path.join(str(tmp_path), "driver.hip")
-    with open(text, "w") as f:
+    subprocess.run([hipcc, *FLAGS, "-c", "-o", obj, src], check=True)
+    return obj
+
+
+_library = []   # the library's objects, compiled once per test session
+
+
+def _library_objects(tmp_path_factory):
+    if not _library:
+        out = str(tmp_path_factory.mktemp("hostcode"))
+        srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip"))) + [os.path.join(HERE, "_fake_hip.cpp")]
+        with ThreadPoolExecutor(max_workers=4) as ex:
+            objs = list(ex.map(lambda s: _compile(s, os.path.join(out, os.path.basename(s) + ".o")), srcs))
+        # the device code that the host objects refer to is not built: empty stand-ins
+        und = subprocess.run(["nm", "-u", *objs], capture_output=True, text=True, check=True).stdout
+        names = sorted({w for w in und.split() if w.startswith("__hip_fatbin_")})
+        stubs = os.path.join(out, "stubs.c")
+        with open(stubs, "w") as f:
+            f.write("".join(f"char {n}[8];\n" for n in names))
+        subprocess.run(["gcc", "-fPIC", "-c", "-o", stubs + ".o", stubs], check=True)
+        _library.extend([*objs, stubs + ".o"])
+    return _library
+
+
+def run(tmp_path_factory, driver, library=False):
+    out = str(tmp_path_factory.mktemp("driver"))
+    src = os.path.join(out, "driver.cpp")
+    with open(src, "w") as f:
         f.write(driver)
-    objs = []
-    for src in [text] + [os.path.join(CSRC, s) for s in sources]:
-        obj = os.path.join(str(tmp_path), os.path.basename(src) + ".o")
-        subprocess.run([hipcc, "--offload-arch=gfx950", "--cuda-host-only", "-O0", "-std=c++17", "-fPIC", "-w",
-                        "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", "-o", obj, src], check=True)
-        objs.append(obj)
-    exe = os.path.join(str(tmp_path), "driver")
-    subprocess.run(["g++", "-o", exe, *objs], check=True)
-    p = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    objs = [_compile(src, src + ".o")] + (list(_library_objects(tmp_path_factory)) if library else [])
+    exe = os.path.join(out, "driver")
+    subprocess.run(["g++", "-o", exe, *objs, "-lpthread"], check=True)
+    p = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert p.returncode == 0, (p.returncode, p.stdout[-2000:], p.stderr[-2000:])
     return p.stdout
