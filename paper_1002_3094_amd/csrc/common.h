@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstddef>
 #include <cstdint>
 #include <new>
@@ -37,6 +38,27 @@ void clear_last_error();
     do {                                                                             \
         if (!(cond)) throw ::axipcg::Error{AXIPCG_EINVAL, (text)};                   \
     } while (0)
+
+// Dynamic LDS above the default 64 KiB needs a kernel's limit raised, on each
+// device it is launched on: one static object per kernel remembers where that was
+// done.  Threads may race to it, the limit is then set twice.
+class LdsLimit {
+    std::atomic<unsigned long long> devices_{0};   // a bit each; devices past 63 set it every time
+
+public:
+    // for a launch with `bytes`; `most` covers every later one's (kernels' static
+    // LDS is under 1 KiB)
+    void raise(const void *fn, size_t bytes, size_t most)
+    {
+        if (bytes <= 65536 - 1024) return;
+        int dev = 0;
+        AXI_CHECK_HIP(hipGetDevice(&dev));
+        const unsigned long long bit = dev < 64 ? 1ull << dev : 0;
+        if (devices_.load(std::memory_order_acquire) & bit) return;
+        AXI_CHECK_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes > most ? bytes : most)));
+        devices_.fetch_or(bit, std::memory_order_release);
+    }
+};
 
 // ---------------------------------------------------------------------------
 // Device-side PCG scalars.  No kernel both reads and writes a field: every

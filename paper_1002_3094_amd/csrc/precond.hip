@@ -168,15 +168,6 @@ inline int transform_rows(int nr, int nz, int prec)
     return (prec == AXIPCG_PREC_FP64 && nr % 2 == 0) ? 2 : 1;
 }
 
-// Dynamic LDS above the default 64 KiB (FP64 rows of 4096) needs the
-// kernel's attribute, set once per kernel.
-inline void allow_transform_lds(const void *fn, size_t bytes, bool &done)
-{
-    if (done || bytes <= 65536) return;
-    AXI_CHECK_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-    done = true;
-}
-
 template <typename T, int BC, bool TWL, int ROWS>
 void zfwd_ttr(const Operator &op, const ZfwdArgs &a, hipStream_t s)
 {
@@ -185,9 +176,9 @@ void zfwd_ttr(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     const size_t shm = transform_lds<T>(N);
     const int thr = fft_threads(N);
     const dim3 grid(op.nr / ROWS);
-    static bool lds_set[2] = {false, false};
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zfwd<T, BC, true, TWL, ROWS>), shm, lds_set[0]);
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zfwd<T, BC, false, TWL, ROWS>), shm, lds_set[1]);
+    static LdsLimit limit[2];
+    limit[0].raise(reinterpret_cast<const void *>(&k_zfwd<T, BC, true, TWL, ROWS>), shm, shm);
+    limit[1].raise(reinterpret_cast<const void *>(&k_zfwd<T, BC, false, TWL, ROWS>), shm, shm);
     if (a.fused)
         hipLaunchKernelGGL((k_zfwd<T, BC, true, TWL, ROWS>), grid, dim3(thr), shm, s, nullptr, a.r, a.q, a.state, op.partials, a.n_pq, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
     else
@@ -231,9 +222,9 @@ void zfwd8_t(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     using F = BlockFft<T, N>;
     const auto tb = tables<T>(op);
     const dim3 grid((op.nr + ROWS - 1) / ROWS), block(F::NT);
-    static bool lds_set[2] = {false, false};
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zfwd8<T, BC, true, N, ROWS>), F::LDS, lds_set[0]);
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zfwd8<T, BC, false, N, ROWS>), F::LDS, lds_set[1]);
+    static LdsLimit limit[2];
+    limit[0].raise(reinterpret_cast<const void *>(&k_zfwd8<T, BC, true, N, ROWS>), F::LDS, F::LDS);
+    limit[1].raise(reinterpret_cast<const void *>(&k_zfwd8<T, BC, false, N, ROWS>), F::LDS, F::LDS);
     if (a.fused)
         hipLaunchKernelGGL((k_zfwd8<T, BC, true, N, ROWS>), grid, block, F::LDS, s, nullptr, a.r, a.q, a.state,
                            op.partials, a.n_pq, (T *)op.spec, tb.tw, tb.pt, op.nr);
@@ -272,12 +263,12 @@ void zinv_ttr(const Operator &op, const ZinvArgs &a, hipStream_t s)
     const size_t shm = transform_lds<T>(N);
     const int thr = fft_threads(N);
     const dim3 grid(op.nr / ROWS);
-    static bool lds_set[5] = {false, false, false, false, false};
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zinv<T, BC, 0, TWL, ROWS>), shm, lds_set[0]);
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zinv<T, BC, 1, TWL, ROWS>), shm, lds_set[1]);
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zinv<T, BC, 2, TWL, ROWS>), shm, lds_set[2]);
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zinv<T, BC, 3, TWL, ROWS>), shm, lds_set[3]);
-    allow_transform_lds(reinterpret_cast<const void *>(&k_zinv<T, BC, 4, TWL, ROWS>), shm, lds_set[4]);
+    static LdsLimit limit[5];
+    limit[0].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 0, TWL, ROWS>), shm, shm);
+    limit[1].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 1, TWL, ROWS>), shm, shm);
+    limit[2].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 2, TWL, ROWS>), shm, shm);
+    limit[3].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 3, TWL, ROWS>), shm, shm);
+    limit[4].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 4, TWL, ROWS>), shm, shm);
     switch (a.mode) {
     case 0:
         hipLaunchKernelGGL((k_zinv<T, BC, 0, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 0> *)a.zout,
@@ -344,8 +335,8 @@ void zinv8_t(const Operator &op, const ZinvArgs &a, hipStream_t s)
     const dim3 grid((op.nr + ROWS - 1) / ROWS), block(F::NT);
 #define AXI_ZINV8(MD, Z, RR, ST, PR, D)                                                                             \
     do {                                                                                                           \
-        static bool lds_set = false;                                                                               \
-        allow_transform_lds(reinterpret_cast<const void *>(&k_zinv8<T, BC, MD, N, ROWS>), F::LDS, lds_set);         \
+        static LdsLimit limit;                                                                                     \
+        limit.raise(reinterpret_cast<const void *>(&k_zinv8<T, BC, MD, N, ROWS>), F::LDS, F::LDS);                  \
         hipLaunchKernelGGL((k_zinv8<T, BC, MD, N, ROWS>), grid, block, F::LDS, s, (const T *)op.spec,               \
                            (ZOut<T, MD> *)(Z), RR, ST, op.partials, PR, tb.tw, tb.pt, op.nr, D, a.tau, a.rho2, a.fin); \
     } while (0)
@@ -417,12 +408,8 @@ void tridiag_t(const Operator &op, const TriGate &gate, hipStream_t s)
     T *spec = (T *)op.spec;
 #define AXI_TRI(LM, U)                                                                                   \
     do {                                                                                                 \
-        static bool lds_set = false;                                                                     \
-        if (g.shm > 65536 && !lds_set) {                                                                 \
-            AXI_CHECK_HIP(hipFuncSetAttribute((const void *)k_tridiag<T, LM, U>,                          \
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)TRI_LDS_MAX)); \
-            lds_set = true;                                                                              \
-        }                                                                                                \
+        static LdsLimit limit;                                                                           \
+        limit.raise((const void *)k_tridiag<T, LM, U>, g.shm, TRI_LDS_MAX);                              \
         hipLaunchKernelGGL((k_tridiag<T, LM, U>), grid, block, g.shm, s, spec, tb.cb, tb.db, tb.rw, tb.lam, \
                            gate.state, op.partials, gate, op.nr, op.nz, g.M, g.S, g.pitch, g.Lp);          \
     } while (0)

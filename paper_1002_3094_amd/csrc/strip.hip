@@ -288,17 +288,6 @@ int red_mt_for(int nr, int G)
     return mt;
 }
 
-// Dynamic LDS above the default 64 KiB needs the kernel's attribute, set
-// once per kernel.
-void allow_lds(const void *fn, size_t bytes, bool &done)
-{
-    if (done || bytes <= 65536) return;
-    // (the kernels' own static LDS is under 1 KiB of the 160)
-    const int most = 159 * 1024;
-    AXI_CHECK_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes < most ? most : (int)bytes));
-    done = true;
-}
-
 template <typename T, int BC, int R2, int R>
 void fwd_r(const Operator &op, const ZfwdArgs &a, hipStream_t s)
 {
@@ -345,8 +334,8 @@ void red_launch_f(const Operator &op, const TriGate &g, hipStream_t s)
     const RedBufs<T> rb = red_bufs<T>(op, 4);
     const int G = strip_count(op.nr, 4);
     const size_t shm = strip_fac_lds<T>(G, MT);
-    static bool lds_set = false;
-    allow_lds(reinterpret_cast<const void *>(&k_strip_reduced_f<T, LM, MT>), shm, lds_set);
+    static LdsLimit limit;
+    limit.raise(reinterpret_cast<const void *>(&k_strip_reduced_f<T, LM, MT>), shm, 159 * 1024);
     hipLaunchKernelGGL((k_strip_reduced_f<T, LM, MT>), dim3(op.nz / MT), dim3(64 * MT), shm, s, rb.e, rb.g, rb.x,
                        fac_of<T>(op), lines_of<T>(op).cb, g.state, op.partials, g, op.nz, G);
     AXI_CHECK_HIP(hipGetLastError());
@@ -358,8 +347,8 @@ void red_launch_mt(const Operator &op, const TriGate &g, hipStream_t s)
     const RedBufs<T> rb = red_bufs<T>(op, R);
     const int G = strip_count(op.nr, R), rows = G * R;
     const size_t shm = strip_red_lds<T>(rows, G, MT);
-    static bool lds_set = false;
-    allow_lds(reinterpret_cast<const void *>(&k_strip_reduced<T, R, LM, MT>), shm, lds_set);
+    static LdsLimit limit;
+    limit.raise(reinterpret_cast<const void *>(&k_strip_reduced<T, R, LM, MT>), shm, 159 * 1024);
     hipLaunchKernelGGL((k_strip_reduced<T, R, LM, MT>), dim3(op.nz / MT), dim3(64 * MT), shm, s, rb.e, rb.g, rb.x,
                        lines_of<T>(op), g.state, op.partials, g, rows, op.nz, G);
     AXI_CHECK_HIP(hipGetLastError());

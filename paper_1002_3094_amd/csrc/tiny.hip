@@ -433,13 +433,10 @@ __global__ void __launch_bounds__(TINY_THREADS) k_pcg_tiny(TinyArgs<T> A)
 template <typename T, int N>
 void tiny_launch_n(const TinyArgs<T> &a, hipStream_t s)
 {
-    static bool lds_set = false;
-    if (!lds_set) {   // the static sums are 512 bytes of the 160 KiB
-        AXI_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_pcg_tiny<T, N>),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, 159 * 1024));
-        lds_set = true;
-    }
-    hipLaunchKernelGGL((k_pcg_tiny<T, N>), dim3(1), dim3(TINY_THREADS), (tiny_lds<T, N>(a.nr)), s, a);
+    const size_t shm = tiny_lds<T, N>(a.nr);
+    static LdsLimit limit;
+    limit.raise(reinterpret_cast<const void *>(&k_pcg_tiny<T, N>), shm, 159 * 1024);   // (512 bytes are the static sums)
+    hipLaunchKernelGGL((k_pcg_tiny<T, N>), dim3(1), dim3(TINY_THREADS), shm, s, a);
     AXI_CHECK_HIP(hipGetLastError());
 }
 
