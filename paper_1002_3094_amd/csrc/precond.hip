@@ -442,7 +442,8 @@ static int strip_handle_rows(const Operator &op, int prec)
 
 // The solves leave strips for block-wide transforms and the per-mode r-solve
 // (0 returned) at up to 512 FP32 rows of 2048 points, unless the handle's strips
-// were set or its single launches, which are strips, are on: the strips' one-wave
+// were set or its single launches, which are whole strips of four rows, are on and
+// can serve the row count: the strips' one-wave
 // transforms (32 points a lane) then occupy half of the 1024 SIMDs or fewer, one
 // wave each, and the r-solve's lines are short.  PCG solves, strips and block-wide
 // (us): 48 rows 1001 and 686, 256 rows 1186 and 864, 512 rows 1360 and 1205, 777
@@ -450,7 +451,8 @@ static int strip_handle_rows(const Operator &op, int prec)
 // and 1315, of 777 1880 and 2012.
 int strip_solve_rows(const Operator &op, int prec)
 {
-    if (prec == AXIPCG_PREC_FP32 && op.nz == 2048 && op.nr <= 512 && !op.strips_set && !op.fused_enabled) return 0;
+    const bool single = op.fused_enabled && op.nr % 4 == 0;
+    if (prec == AXIPCG_PREC_FP32 && op.nz == 2048 && op.nr <= 512 && !op.strips_set && !single) return 0;
     return strip_handle_rows(op, prec);
 }
 
