@@ -86,23 +86,25 @@ __global__ void __launch_bounds__(64 * R) k_strip_one(OneArgs<T> A)
     if (!grid_sync(A.bar, A.G, 2u * A.epoch + 1u, &flag)) return fail();
     if (PCG && tridiag_gate(A.st, A.partials, A.g, red, s) != ST_RUN) return;
     const int l0 = s * A.mpw, cnt = N - l0 < A.mpw ? N - l0 : A.mpw;
-    if (cnt > 0 && R == 4) {
-        // the factored systems, in the operations of the three-launch form
-        stage_red<T, false>(A.red_e, A.red_g, N, A.G, l0, cnt, base2);
-        __syncthreads();
-        const int lane = threadIdx.x & 63;
-        int S, lo, m;
-        red_lane(A.G, lane, S, lo, m);
-        for (int w = threadIdx.x >> 6; w < cnt; w += R) {
-            RedFac<T, LMAX> f;
-            f.load(A.fac, l0 + w, red_rows(A.G), A.ln.cb, lo, m, lane);
-            f.solve(base2 + w * A.G, base2 + (cnt + w) * A.G, A.G, lo, m, S, lane);
+    if (cnt > 0) {
+        if constexpr (R == 4) {
+            // the factored systems, in the operations of the three-launch form
+            stage_red<T, false>(A.red_e, A.red_g, N, A.G, l0, cnt, base2);
+            __syncthreads();
+            const int lane = threadIdx.x & 63;
+            int S, lo, m;
+            red_lane(A.G, lane, S, lo, m);
+            for (int w = threadIdx.x >> 6; w < cnt; w += R) {
+                RedFac<T, LMAX> f;
+                f.load(A.fac, l0 + w, red_rows(A.G), A.ln.cb, lo, m, lane);
+                f.solve(base2 + w * A.G, base2 + (cnt + w) * A.G, A.G, lo, m, S, lane);
+            }
+            store_red<T, false>(A.red_x, N, A.G, l0, cnt, base2);
+        } else {
+            strip_stage2<T, false>(A.red_e, A.red_g, A.ln, A.nr, N, A.G, l0, cnt, base2);
+            __syncthreads();
+            strip_solve2<T, R, LMAX, false>(A.red_x, A.ln, A.nr, N, A.G, l0, cnt, base2);
         }
-        store_red<T, false>(A.red_x, N, A.G, l0, cnt, base2);
-    } else if (cnt > 0) {
-        strip_stage2<T, false>(A.red_e, A.red_g, A.ln, A.nr, N, A.G, l0, cnt, base2);
-        __syncthreads();
-        strip_solve2<T, R, LMAX, false>(A.red_x, A.ln, A.nr, N, A.G, l0, cnt, base2);
     }
     if (!grid_sync(A.bar, A.G, 2u * A.epoch + 2u, &flag)) return fail();
     strip_phase3<T, BC, PCG ? 1 : 0, R2, R>(nullptr, A.red_x, zout, A.r, A.st, A.partials, false, A.tw, A.pt,

@@ -10,17 +10,18 @@ namespace axipcg {
 
 namespace {
 
-template <typename T, int BC, bool FUSED, bool TWLDS, int ROWS>
+// (rows of up to 128 points, whose twiddles fit LDS)
+template <typename T, int BC, bool FUSED, int ROWS>
 __global__ void __launch_bounds__(256)
 k_zfwd(const double *__restrict__ rin, double *__restrict__ r, const double *__restrict__ q, PcgState *st,
        double *__restrict__ partials, int n_pq,
        T *__restrict__ spec, const typename vec2_of<T>::type *__restrict__ tw,
        const typename vec2_of<T>::type *__restrict__ pt, int nr, int N)
 {
-    zfwd_body<T, BC, FUSED, TWLDS, ROWS>(rin, r, q, st, partials, n_pq, spec, tw, pt, nr, N, blockIdx.x);
+    zfwd_body<T, BC, FUSED, true, ROWS>(rin, r, q, st, partials, n_pq, spec, tw, pt, nr, N, blockIdx.x);
 }
 
-template <typename T, int BC, int MODE, bool TWLDS, int ROWS>
+template <typename T, int BC, int MODE, int ROWS>
 __global__ void __launch_bounds__(256)
 k_zinv(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout, const double *__restrict__ r,
        const PcgState *st, double *__restrict__ partials, bool pr,
@@ -28,7 +29,7 @@ k_zinv(const T *__restrict__ spec, ZOut<T, MODE> *__restrict__ zout, const doubl
        const typename vec2_of<T>::type *__restrict__ pt, int nr, int N, double *__restrict__ dinc, double tau,
        double rho2, XFin fin)
 {
-    zinv_body<T, BC, MODE, TWLDS, ROWS>(spec, zout, r, st, partials, pr, tw, pt, nr, N, blockIdx.x, dinc, tau, rho2, fin);
+    zinv_body<T, BC, MODE, true, ROWS>(spec, zout, r, st, partials, pr, tw, pt, nr, N, blockIdx.x, dinc, tau, rho2, fin);
 }
 
 template <typename T, int BC, bool FUSED, int N, int ROWS>
@@ -168,7 +169,7 @@ inline int transform_rows(int nr, int nz, int prec)
     return (prec == AXIPCG_PREC_FP64 && nr % 2 == 0) ? 2 : 1;
 }
 
-template <typename T, int BC, bool TWL, int ROWS>
+template <typename T, int BC, int ROWS>
 void zfwd_ttr(const Operator &op, const ZfwdArgs &a, hipStream_t s)
 {
     const int N = op.nz;
@@ -176,13 +177,10 @@ void zfwd_ttr(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     const size_t shm = transform_lds<T>(N);
     const int thr = fft_threads(N);
     const dim3 grid(op.nr / ROWS);
-    static LdsLimit limit[2];
-    limit[0].raise(reinterpret_cast<const void *>(&k_zfwd<T, BC, true, TWL, ROWS>), shm, shm);
-    limit[1].raise(reinterpret_cast<const void *>(&k_zfwd<T, BC, false, TWL, ROWS>), shm, shm);
     if (a.fused)
-        hipLaunchKernelGGL((k_zfwd<T, BC, true, TWL, ROWS>), grid, dim3(thr), shm, s, nullptr, a.r, a.q, a.state, op.partials, a.n_pq, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
+        hipLaunchKernelGGL((k_zfwd<T, BC, true, ROWS>), grid, dim3(thr), shm, s, nullptr, a.r, a.q, a.state, op.partials, a.n_pq, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
     else
-        hipLaunchKernelGGL((k_zfwd<T, BC, false, TWL, ROWS>), grid, dim3(thr), shm, s, a.rin, nullptr, nullptr, a.state, op.partials, 0, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
+        hipLaunchKernelGGL((k_zfwd<T, BC, false, ROWS>), grid, dim3(thr), shm, s, a.rin, nullptr, nullptr, a.state, op.partials, 0, (T *)op.spec, tb.tw, tb.pt, op.nr, N);
     AXI_CHECK_HIP(hipGetLastError());
 }
 
@@ -250,12 +248,12 @@ void zfwd_t(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     }
     // rows of up to 128 points, whose twiddles fit LDS
     if constexpr (sizeof(T) == 8) {
-        if (rows == 2) return zfwd_ttr<T, BC, true, 2>(op, a, s);
+        if (rows == 2) return zfwd_ttr<T, BC, 2>(op, a, s);
     }
-    zfwd_ttr<T, BC, true, 1>(op, a, s);
+    zfwd_ttr<T, BC, 1>(op, a, s);
 }
 
-template <typename T, int BC, bool TWL, int ROWS>
+template <typename T, int BC, int ROWS>
 void zinv_ttr(const Operator &op, const ZinvArgs &a, hipStream_t s)
 {
     const int N = op.nz;
@@ -263,31 +261,25 @@ void zinv_ttr(const Operator &op, const ZinvArgs &a, hipStream_t s)
     const size_t shm = transform_lds<T>(N);
     const int thr = fft_threads(N);
     const dim3 grid(op.nr / ROWS);
-    static LdsLimit limit[5];
-    limit[0].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 0, TWL, ROWS>), shm, shm);
-    limit[1].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 1, TWL, ROWS>), shm, shm);
-    limit[2].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 2, TWL, ROWS>), shm, shm);
-    limit[3].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 3, TWL, ROWS>), shm, shm);
-    limit[4].raise(reinterpret_cast<const void *>(&k_zinv<T, BC, 4, TWL, ROWS>), shm, shm);
     switch (a.mode) {
     case 0:
-        hipLaunchKernelGGL((k_zinv<T, BC, 0, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 0> *)a.zout,
+        hipLaunchKernelGGL((k_zinv<T, BC, 0, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 0> *)a.zout,
                            nullptr, nullptr, op.partials, false, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0, a.fin);
         break;
     case 1:
-        hipLaunchKernelGGL((k_zinv<T, BC, 1, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 1> *)a.zout,
+        hipLaunchKernelGGL((k_zinv<T, BC, 1, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 1> *)a.zout,
                            a.r, a.state, op.partials, a.pr, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0, a.fin);
         break;
     case 2:
-        hipLaunchKernelGGL((k_zinv<T, BC, 2, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 2> *)a.zout,
+        hipLaunchKernelGGL((k_zinv<T, BC, 2, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, (ZOut<T, 2> *)a.zout,
                            a.r, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, nullptr, 0.0, 0.0, a.fin);
         break;
     case 3:
-        hipLaunchKernelGGL((k_zinv<T, BC, 3, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, nullptr,
+        hipLaunchKernelGGL((k_zinv<T, BC, 3, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, nullptr,
                            nullptr, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, a.d, a.tau, a.rho2, a.fin);
         break;
     default:
-        hipLaunchKernelGGL((k_zinv<T, BC, 4, TWL, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, nullptr,
+        hipLaunchKernelGGL((k_zinv<T, BC, 4, ROWS>), grid, dim3(thr), shm, s, (const T *)op.spec, nullptr,
                            nullptr, a.state, op.partials, false, tb.tw, tb.pt, op.nr, N, a.d, a.tau, a.rho2, a.fin);
         break;
     }
@@ -366,9 +358,9 @@ void zinv_t(const Operator &op, const ZinvArgs &a, hipStream_t s)
         return rows == 2 ? zinv8_t<T, BC, 4096, 2>(op, a, s) : zinv8_t<T, BC, 4096, 1>(op, a, s);
     }
     if constexpr (sizeof(T) == 8) {
-        if (rows == 2) return zinv_ttr<T, BC, true, 2>(op, a, s);
+        if (rows == 2) return zinv_ttr<T, BC, 2>(op, a, s);
     }
-    zinv_ttr<T, BC, true, 1>(op, a, s);
+    zinv_ttr<T, BC, 1>(op, a, s);
 }
 
 // LDS of an r-solve workgroup (its [M][N_r] tile, padded): up to 136 KiB, so

@@ -374,13 +374,13 @@ void red_r(const Operator &op, const TriGate &g, hipStream_t s)
         case 8: return red_launch_f<T, 8, red_mt<T>()>(op, g, s);
         default: return red_launch_f<T, 16, red_mt<T>()>(op, g, s);
         }
+    } else {   // at most 512 strips of eight rows
+        const int per = (strip_count(op.nr, R) + 63) / 64;
+        if (per <= 1) red_launch<T, R, 1>(op, g, s);
+        else if (per <= 2) red_launch<T, R, 2>(op, g, s);
+        else if (per <= 4) red_launch<T, R, 4>(op, g, s);
+        else red_launch<T, R, 8>(op, g, s);
     }
-    const int per = (strip_count(op.nr, R) + 63) / 64;
-    if (per <= 1) red_launch<T, R, 1>(op, g, s);
-    else if (per <= 2) red_launch<T, R, 2>(op, g, s);
-    else if (per <= 4) red_launch<T, R, 4>(op, g, s);
-    else if (per <= 8) red_launch<T, R, 8>(op, g, s);
-    else red_launch<T, R, 16>(op, g, s);
 }
 
 template <typename T>

@@ -17,6 +17,12 @@ static std::map<const void *, std::string> &names()
     static std::map<const void *, std::string> m;
     return m;
 }
+std::vector<std::string> kernels()
+{
+    std::vector<std::string> all;
+    for (auto &n : names()) all.push_back(n.second);
+    return all;
+}
 static std::string name_of(const void *fn)
 {
     auto it = names().find(fn);

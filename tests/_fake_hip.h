@@ -23,6 +23,7 @@ extern std::vector<Launch> launches;
 extern std::vector<Limit> limits;
 extern std::vector<size_t> mallocs;
 extern int device;        // the current one
+std::vector<std::string> kernels();   // every kernel that the library holds
 
 inline bool has(const std::string &s, const char *part) { return s.find(part) != std::string::npos; }
 
