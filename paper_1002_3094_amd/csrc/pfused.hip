@@ -155,7 +155,8 @@ bool pfused_plan(Operator &op, int kind)
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return false;
     const int mpw = (N + G - 1) / G;
-    const size_t shm = (size_t)R * (r2_of(N) * 72) * sizeof(cx<float>) + strip_red_lds<float>(nr, G, mpw);
+    const size_t red = R == 4 ? strip_fac_lds<float>(G, mpw) : strip_red_lds<float>(nr, G, mpw);
+    const size_t shm = (size_t)R * (r2_of(N) * 72) * sizeof(cx<float>) + red;
     if (shm > 160 * 1024) return false;
     void *fn = nullptr;
     if (op.bc_z == DIR) fn = kind == 0 ? one_kernel<DIR, 0>(N, R) : one_kernel<DIR, 1>(N, R);

@@ -344,13 +344,13 @@ __device__ inline void red_lane(int G, int lane, int &S, int &lo, int &m)
 // LDS of the reduced-system phase: the r-line arrays (padded, LdsLines) and
 // the reduced data of `mt` modes, [mt][G] each for E1 and G0.
 template <typename T>
-__host__ __device__ inline size_t strip_red_lds(int nr, int G, int mt)
+__host__ __device__ constexpr size_t strip_red_lds(int nr, int G, int mt)
 {
     return (3 * (size_t)(nr + nr / 32 + 1) + 2 * (size_t)mt * G) * sizeof(T);
 }
 // The same with the factored coefficients: the reduced data only.
 template <typename T>
-__host__ __device__ inline size_t strip_fac_lds(int G, int mt) { return 2 * (size_t)mt * G * sizeof(T); }
+__host__ __device__ constexpr size_t strip_fac_lds(int G, int mt) { return 2 * (size_t)mt * G * sizeof(T); }
 
 // (nr here and in strip_solve2: G strips' rows, the padded ones included.)
 // Phase 2 (K2) part 1: stage the r-line arrays and the reduced data of modes

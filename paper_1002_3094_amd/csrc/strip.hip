@@ -277,16 +277,12 @@ RedBufs<T> red_bufs(const Operator &op, int R)
 // modes per reduced-system workgroup: 32 bytes of each strip's row
 template <typename T>
 constexpr int red_mt() { return 32 / (int)sizeof(T); }
-// Modes per workgroup for nr rows in G strips: red_mt, halved (down to 2)
-// only while the LDS stage would not fit (FP64 with 1024 strips).  Fewer
-// modes per workgroup than red_mt made PCG iterations slower at 1024^2.
-template <typename T>
-int red_mt_for(int nr, int G)
-{
-    int mt = red_mt<T>();
-    while (mt > 2 && strip_red_lds<T>(nr, G, mt) > 160 * 1024) mt /= 2;
-    return mt;
-}
+// They fit LDS on every grid that strips take: the reduced data alone in strips of
+// four rows, with the r-line arrays in strips of eight.  (Fewer modes per workgroup
+// made PCG iterations slower at 1024^2.)
+static_assert(strip_fac_lds<float>(1024, red_mt<float>()) <= 65536 && strip_fac_lds<double>(1024, red_mt<double>()) <= 65536);
+static_assert(strip_red_lds<float>(4096, 512, red_mt<float>()) <= 159 * 1024 &&
+              strip_red_lds<double>(4096, 512, red_mt<double>()) <= 159 * 1024);
 
 template <typename T, int BC, int R2, int R>
 void fwd_r(const Operator &op, const ZfwdArgs &a, hipStream_t s)
@@ -341,9 +337,10 @@ void red_launch_f(const Operator &op, const TriGate &g, hipStream_t s)
     AXI_CHECK_HIP(hipGetLastError());
 }
 
-template <typename T, int R, int LM, int MT>
-void red_launch_mt(const Operator &op, const TriGate &g, hipStream_t s)
+template <typename T, int R, int LM>
+void red_launch(const Operator &op, const TriGate &g, hipStream_t s)
 {
+    constexpr int MT = red_mt<T>();
     const RedBufs<T> rb = red_bufs<T>(op, R);
     const int G = strip_count(op.nr, R), rows = G * R;
     const size_t shm = strip_red_lds<T>(rows, G, MT);
@@ -354,19 +351,10 @@ void red_launch_mt(const Operator &op, const TriGate &g, hipStream_t s)
     AXI_CHECK_HIP(hipGetLastError());
 }
 
-template <typename T, int R, int LM>
-void red_launch(const Operator &op, const TriGate &g, hipStream_t s)
-{
-    const int G = strip_count(op.nr, R), mt = red_mt_for<T>(G * R, G);
-    if (mt >= 8) red_launch_mt<T, R, LM, (red_mt<T>() >= 8 ? 8 : 2)>(op, g, s);
-    else if (mt >= 4) red_launch_mt<T, R, LM, 4>(op, g, s);
-    else red_launch_mt<T, R, LM, 2>(op, g, s);
-}
-
 template <typename T, int R>
 void red_r(const Operator &op, const TriGate &g, hipStream_t s)
 {
-    if constexpr (R == 4) {   // the reduced data of red_mt modes always fit LDS
+    if constexpr (R == 4) {
         switch (red_rows(strip_count(op.nr, 4))) {
         case 1: return red_launch_f<T, 1, red_mt<T>()>(op, g, s);
         case 2: return red_launch_f<T, 2, red_mt<T>()>(op, g, s);
@@ -452,15 +440,14 @@ bool usable_t(const Operator &op, int R)
 {
     if (R != 4 && R != 8) return false;
     if (strip_r2<T>(op.nz) == 0) return false;
-    const int G = strip_count(op.nr, R), rows = G * R;
-    return G <= 1024 && strip_red_lds<T>(rows, G, red_mt_for<T>(rows, G)) <= 160 * 1024;
+    return strip_count(op.nr, R) <= 1024;
 }
 
 }  // namespace
 
 // The strip path serves an operator and precision with strips of `rows`
-// rows (4 or 8) when the one-wave transforms cover nz and the reduced system fits one wavefront's registers (at most
-// 1024 strips) and its workgroup's LDS.
+// rows (4 or 8) when the one-wave transforms cover nz and the reduced system fits
+// one wavefront's registers (at most 1024 strips).
 bool strip_usable(const Operator &op, int prec, int rows)
 {
     if (!op.strip_red) return false;
