@@ -243,11 +243,12 @@ __device__ inline void wave_tri(const T (&a)[LMAX], const T (&b)[LMAX], const T 
 // no r-line arrays in LDS.
 //
 // The reduced matrix is symmetric, a_{k+1} = c_k, and stored so.  Factors of
-// mode l, lane `lane` and item k at fac[(l red_items(L) + k) 64 + lane], L the
-// rows per lane the layout was made for: inv[L - 1], c[L], a_0, al[6], ga[6],
-// 1 / (the lane's reduced pivot).
+// mode l, lane `lane` < S and item k at fac[(l red_items(L) + k) S + lane], S the
+// lanes that hold rows and L the rows per lane the layout was made for: inv[L - 1],
+// c[L], a_0, al[6], ga[6], 1 / (the lane's reduced pivot).
 // ---------------------------------------------------------------------------
 __host__ __device__ inline int red_items(int L) { return 2 * L + 13; }
+__host__ __device__ inline int red_lanes(int G) { return G < 64 ? G : 64; }
 // Rows per lane of G strips, up to a power of two (the kernels' register rows).
 __host__ __device__ inline int red_rows(int G)
 {
@@ -259,26 +260,27 @@ __host__ __device__ inline int red_rows(int G)
 template <typename T, int LMAX>
 struct RedFac {
     T inv[LMAX], c[LMAX], cj[LMAX], a0, al[6], ga[6], piv;
-    // rows [lo, lo + m) of the lane; L the layout's rows per lane (L <= LMAX);
-    // cj: the couplings of the interface rows to the next strips
+    // rows [lo, lo + m) of the lane, S lanes with rows; L the layout's rows per
+    // lane (L <= LMAX); cj: the couplings of the interface rows to the next strips
     __device__ __forceinline__ void load(const T *__restrict__ fac, int l, int L, const T *__restrict__ cb, int lo,
-                                         int m, int lane)
+                                         int m, int S, int lane)
     {
-        const T *f = fac + (size_t)l * red_items(L) * 64 + lane;
+        const bool in = lane < S;   // the others: zeros, which solve() turns into zeros
+        const T *f = fac + (size_t)l * red_items(L) * S + lane;
 #pragma unroll
         for (int t = 0; t < LMAX; ++t) {
-            inv[t] = t < L - 1 ? f[t * 64] : (T)0;
-            c[t] = t < L ? f[(L - 1 + t) * 64] : (T)0;
+            inv[t] = in && t < L - 1 ? f[t * S] : (T)0;
+            c[t] = in && t < L ? f[(L - 1 + t) * S] : (T)0;
             cj[t] = t < m ? cb[(lo + t) * 4 + 3] : (T)0;
         }
-        f += (2 * L - 1) * 64;
-        a0 = f[0];
+        f += (2 * L - 1) * S;
+        a0 = in ? f[0] : (T)0;
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-            al[k] = f[(1 + k) * 64];
-            ga[k] = f[(7 + k) * 64];
+            al[k] = in ? f[(1 + k) * S] : (T)0;
+            ga[k] = in ? f[(7 + k) * S] : (T)0;
         }
-        piv = f[13 * 64];
+        piv = in ? f[13 * S] : (T)0;
     }
     // te, tg: E1 and G0 of the mode's strips (LDS); the solution replaces te
     // (every lane has read its values of te before any is written).
@@ -336,7 +338,7 @@ struct RedFac {
 // The lane's rows [lo, lo + m) of G strips over S lanes.
 __device__ inline void red_lane(int G, int lane, int &S, int &lo, int &m)
 {
-    S = G < 64 ? G : 64;
+    S = red_lanes(G);
     lo = lane < S ? (int)(((long)lane * G) / S) : G;
     m = (lane < S ? (int)(((long)(lane + 1) * G) / S) : G) - lo;
 }

@@ -102,7 +102,7 @@ k_strip_reduced_f(const T *__restrict__ red_e, const T *__restrict__ red_g, T *_
     int S, lo, m;
     red_lane(G, lane, S, lo, m);
     RedFac<T, LMAX> f;
-    f.load(fac, l0 + w, LMAX, cb, lo, m, lane);
+    f.load(fac, l0 + w, LMAX, cb, lo, m, S, lane);
     stage_red<T, VEC>(red_e, red_g, N, G, l0, MT, te);
     if (g.mode != 0 && tridiag_gate(st, partials, g, red, blockIdx.x, g.mode == 1 ? &pre : nullptr) != ST_RUN)
         return;
@@ -163,7 +163,7 @@ k_strip_factors(Lines<T> ln, T *__restrict__ fac, int G)
             c[k] = -cj * wn;
         }
     }
-    T *f = fac + (size_t)l * red_items(LMAX) * 64 + lane;
+    T *f = fac + (size_t)l * red_items(LMAX) * S + lane;   // (lanes < S store)
     double vl = 0, wl = 0, v0 = 0, w0 = 1, vp[LMAX], cq[LMAX];
 #pragma unroll
     for (int t = 0; t < LMAX; ++t) {
@@ -175,11 +175,11 @@ k_strip_factors(Lines<T> ln, T *__restrict__ fac, int G)
             vl = vp[t];
             wl = cq[t];
         }
-        if (t < LMAX - 1) f[t * 64] = (T)inv;
-        f[(LMAX - 1 + t) * 64] = (T)c[t];
+        if (active && t < LMAX - 1) f[t * S] = (T)inv;
+        if (active) f[(LMAX - 1 + t) * S] = (T)c[t];
     }
-    f += (2 * LMAX - 1) * 64;
-    f[0] = (T)a[0];
+    f += (2 * LMAX - 1) * S;
+    if (active) f[0] = (T)a[0];
     if (m >= 2) {
         v0 = vl;
         w0 = wl;
@@ -215,10 +215,12 @@ k_strip_factors(Lines<T> ln, T *__restrict__ fac, int G)
             ra = hm ? al * am : 0.0;
             rc = hp ? ga * cp : 0.0;
         }
-        f[(1 + q) * 64] = (T)al;
-        f[(7 + q) * 64] = (T)ga;
+        if (active) {
+            f[(1 + q) * S] = (T)al;
+            f[(7 + q) * S] = (T)ga;
+        }
     }
-    f[13 * 64] = (T)(active ? 1.0 / rb : 0.0);
+    if (active) f[13 * S] = (T)(1.0 / rb);
 }
 
 template <typename T, int BC, int MODE, int R2, int R>
@@ -462,7 +464,7 @@ static void factors_t(const Operator &op, T **fac, hipStream_t s)
     if (strip_r2<T>(op.nz) == 0 || strip_count(op.nr, 4) > 1024) return;
     const int G = strip_count(op.nr, 4), L = red_rows(G);
     void *p = nullptr;
-    const hipError_t e = hipMalloc(&p, sizeof(T) * (size_t)op.nz * red_items(L) * 64);
+    const hipError_t e = hipMalloc(&p, sizeof(T) * (size_t)op.nz * red_items(L) * red_lanes(G));
     if (e != hipSuccess) throw Error{AXIPCG_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e)};
     *fac = static_cast<T *>(p);
 #define AXI_FAC(LM) hipLaunchKernelGGL((k_strip_factors<T, LM>), dim3(op.nz), dim3(64), 0, s, lines_of<T>(op), *fac, G)

@@ -58,3 +58,34 @@ def test_single_launch_lds(tmp_path_factory):
 
     eight = 8 * (2048 // 128 * 72) * 8 + (3 * (512 + 512 // 32 + 1) + 2 * 32 * 64) * 4   # the r-line arrays too
     assert out == [(128, four(256)), (128, four(256)), (64, eight), (128, four(2048))]
+
+
+MEMORY = r"""
+#include <cstdio>
+#include "_fake_hip.h"
+#include "axipcg.h"
+int main()
+{
+    for (int nr : {2, 32, 255, 1024}) {
+        const size_t n = (size_t)nr * 256;
+        std::vector<double> kappa(n, 1.0), q(n, 0.5);
+        fake::mallocs.clear();
+        axipcg_op_t op = nullptr;
+        if (axipcg_op_create(nr, 256, 1, 1, 0, kappa.data(), q.data(), 0, -1, nullptr, &op)) return 2;
+        for (size_t m : fake::mallocs) std::printf("%zu ", m);
+        std::printf("\n");
+        axipcg_op_destroy(op);
+    }
+    return 0;
+}
+"""
+
+
+def test_reduced_factors_take_the_lanes_that_hold_strips(tmp_path_factory):
+    """2 L + 13 values a mode and lane, of 1, 8 and 64 lanes of one strip (L = 1) and 64
+    of four (L = 4), in both precisions: what the solves read and no more."""
+    out = _hostcode.run(tmp_path_factory, MEMORY, library=True).splitlines()
+    for line, (lanes, rows) in zip(out, ((1, 1), (8, 1), (64, 1), (64, 4))):
+        sizes = [int(v) for v in line.split()]
+        for width in (4, 8):
+            assert 256 * (2 * rows + 13) * lanes * width in sizes
