@@ -157,16 +157,17 @@ template <typename T>
 size_t transform_lds(int N) { return (twiddles_in_lds<T>(N) ? 3 : 2) * (size_t)N * sizeof(cx<T>); }
 
 // Rows per transform workgroup of the block-wide forms: two, which share one
-// complex FFT, when that still leaves at least 256 workgroups, else one; the
-// FP32 Stockham form (rows of up to 128 points) takes one, its FFT being too
-// short to hide a second row's loads behind.  Rows of 2048 and more (bxform.h)
-// pair any nr, the others (xform.h) an even one.
+// complex FFT, when that still leaves at least 256 workgroups, else one.  Sharing
+// puts rounding of the larger row's size into the smaller one: in FP32 that can be
+// all of a row 1e-7 times its partner.  So FP32 rows share only where they are 4096
+// long and even in number; elsewhere it gains little (PCG solves, one row and two:
+// 512 rows of 2048 points 1210 and 1213 us, 513 rows of 4096 2597 and 2393).
 inline bool block8(int nz) { return nz >= 2048; }
 inline int transform_rows(int nr, int nz, int prec)
 {
     if (nr < 512) return 1;
-    if (block8(nz)) return 2;
-    return (prec == AXIPCG_PREC_FP64 && nr % 2 == 0) ? 2 : 1;
+    if (prec == AXIPCG_PREC_FP32) return (nz >= 4096 && nr % 2 == 0) ? 2 : 1;
+    return (block8(nz) || nr % 2 == 0) ? 2 : 1;   // bxform.h pairs any count, xform.h an even one
 }
 
 template <typename T, int BC, int ROWS>
@@ -243,7 +244,12 @@ void zfwd_t(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     }
     const int rows = transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32);
     if (block8(op.nz)) {
-        if (op.nz == 2048) return rows == 2 ? zfwd8_t<T, BC, 2048, 2>(op, a, s) : zfwd8_t<T, BC, 2048, 1>(op, a, s);
+        if (op.nz == 2048) {
+            if constexpr (sizeof(T) == 8) {
+                if (rows == 2) return zfwd8_t<T, BC, 2048, 2>(op, a, s);
+            }
+            return zfwd8_t<T, BC, 2048, 1>(op, a, s);
+        }
         return rows == 2 ? zfwd8_t<T, BC, 4096, 2>(op, a, s) : zfwd8_t<T, BC, 4096, 1>(op, a, s);
     }
     // rows of up to 128 points, whose twiddles fit LDS
@@ -354,7 +360,12 @@ void zinv_t(const Operator &op, const ZinvArgs &a, hipStream_t s)
     }
     const int rows = transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32);
     if (block8(op.nz)) {
-        if (op.nz == 2048) return rows == 2 ? zinv8_t<T, BC, 2048, 2>(op, a, s) : zinv8_t<T, BC, 2048, 1>(op, a, s);
+        if (op.nz == 2048) {
+            if constexpr (sizeof(T) == 8) {
+                if (rows == 2) return zinv8_t<T, BC, 2048, 2>(op, a, s);
+            }
+            return zinv8_t<T, BC, 2048, 1>(op, a, s);
+        }
         return rows == 2 ? zinv8_t<T, BC, 4096, 2>(op, a, s) : zinv8_t<T, BC, 4096, 1>(op, a, s);
     }
     if constexpr (sizeof(T) == 8) {
