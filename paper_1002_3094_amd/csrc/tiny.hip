@@ -43,17 +43,24 @@ struct TinyArgs {
     unsigned seq;
 };
 
-// Complex slots of a row pair: slot i at i + i / 8, which spreads a pass's
-// strided writes over the banks.
+// Rows to a complex FFT: two in FP64.  FP32 rows take one each, as rounding of the
+// larger one's size could be all of a smaller partner.
+template <typename T>
+__host__ __device__ constexpr int tiny_pair() { return sizeof(T) == 8 ? 2 : 1; }
+template <typename T>
+__host__ __device__ constexpr int tiny_ffts(int nr) { return (nr + tiny_pair<T>() - 1) / tiny_pair<T>(); }
+
+// Complex slots of an FFT: slot i at i + i / 8, which spreads a pass's strided
+// writes over the banks.
 template <int N>
 constexpr int tiny_row() { return N + N / 8; }
 
-// LDS: p, the FFT buffer of (nr + 1) / 2 row pairs, the spectra, the pivots, the
-// tables and the r-line couplings.
+// LDS: p, the FFT buffers, the spectra, the pivots, the tables and the r-line
+// couplings.
 template <typename T, int N>
 size_t tiny_lds(int nr)
 {
-    return sizeof(double) * nr * N + sizeof(cx<T>) * ((size_t)(nr + 1) / 2 * tiny_row<N>() + 2 * N) +
+    return sizeof(double) * nr * N + sizeof(cx<T>) * ((size_t)tiny_ffts<T>(nr) * tiny_row<N>() + 2 * N) +
            sizeof(T) * (2 * (size_t)nr * N + nr);
 }
 
@@ -92,15 +99,15 @@ __device__ inline double tiny_sum(double v, double *sm)
     return lane_value(row_sum(sm[threadIdx.x & 15]), 0);
 }
 
-// The FFTs of all row pairs in place, N / 8 threads to a pair; the threads past
-// the last pair take part in the barriers.  The buffer is complete on entry and
+// All FFTs in place, N / 8 threads to each; the threads past the last one take part
+// in the barriers.  The buffer is complete on entry and
 // on exit (barriers included).
 template <typename T, int N>
 struct TinyFft {
     __device__ static int at(int i) { return i + (i >> 3); }
     static constexpr int NT = N / 8;
     template <int RAD, int NS>
-    __device__ static void pass(cx<T> *a, const cx<T> *tw, int j0, bool act)
+    __device__ __forceinline__ static void pass(cx<T> *a, const cx<T> *tw, int j0, bool act)
     {
         constexpr int Q = N / RAD, PER = 8 / RAD;   // butterflies in all, and of a thread
         cx<T> v[8];
@@ -134,10 +141,10 @@ struct TinyFft {
         }
         __syncthreads();
     }
-    __device__ static void run(cx<T> *buf, const cx<T> *tw, int npair, int t)
+    __device__ __forceinline__ static void run(cx<T> *buf, const cx<T> *tw, int nfft, int t)
     {
         const int q = t / NT, j = t & (NT - 1);
-        const bool act = q < npair;
+        const bool act = q < nfft;
         cx<T> *a = buf + (act ? q : 0) * tiny_row<N>();
         pass<8, 1>(a, tw, j, act);
         if constexpr (N == 16) pass<2, 8>(a, tw, j, act);
@@ -152,13 +159,13 @@ __global__ void __launch_bounds__(TINY_THREADS) k_pcg_tiny(TinyArgs<T> A)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     __shared__ double sums[4][16];
-    constexpr int ROW = tiny_row<N>();
+    constexpr int ROW = tiny_row<N>(), PAIR = tiny_pair<T>();
     using F = TinyFft<T, N>;
-    const int nr = A.nr, n = nr * N, t = threadIdx.x, npair = (nr + 1) / 2;
+    const int nr = A.nr, n = nr * N, t = threadIdx.x, nfft = tiny_ffts<T>(nr);
     const bool dir = A.bc == DIR;
     double *ps = reinterpret_cast<double *>(smem_raw);
     cx<T> *buf = reinterpret_cast<cx<T> *>(ps + n);
-    cx<T> *twl = buf + npair * ROW, *ptl = twl + N;
+    cx<T> *twl = buf + nfft * ROW, *ptl = twl + N;
     T *f = reinterpret_cast<T *>(ptl + N), *piv = f + n, *cb = piv + n;   // f: spectra [nr][N]
 
     // this thread's points e = t + 1024 j, row i = e / N, column k = e % N; the
@@ -249,19 +256,25 @@ __global__ void __launch_bounds__(TINY_THREADS) k_pcg_tiny(TinyArgs<T> A)
         for (int j = 0; j < TINY_PPT; ++j) {
             const int e = t + TINY_THREADS * j, i = e / N, k = e & (N - 1);
             if (e >= n) continue;
-            cx<T> *slot = buf + (i >> 1) * ROW + F::at((k & 1) ? N - 1 - (k >> 1) : k >> 1);
+            cx<T> *slot = buf + i / PAIR * ROW + F::at((k & 1) ? N - 1 - (k >> 1) : k >> 1);
             const T v = (dir && (k & 1)) ? -(T)r[j] : (T)r[j];
-            if (i & 1) slot->y = v;
+            if constexpr (PAIR == 1) *slot = {v, (T)0};
+            else if (i & 1) slot->y = v;
             else slot->x = v;
         }
-        if ((nr & 1) && t < N) buf[(npair - 1) * ROW + F::at(t)].y = (T)0;
+        if (PAIR == 2 && (nr & 1) && t < N) buf[(nfft - 1) * ROW + F::at(t)].y = (T)0;
         __syncthreads();
-        F::run(buf, twl, npair, t);
-        for (int e = t; e < npair * N; e += TINY_THREADS) {
+        F::run(buf, twl, nfft, t);
+        for (int e = t; e < nfft * N; e += TINY_THREADS) {
             const int q = e / N, j = e & (N - 1);
             const int m = dir ? N - 1 - j : j;
-            const cx<T> zm = buf[q * ROW + F::at(m)], zc = buf[q * ROW + F::at((N - m) & (N - 1))], w = ptl[m];
+            const cx<T> zm = buf[q * ROW + F::at(m)], w = ptl[m];
             const T sc = nrm * (m == 0 ? half : (T)1);
+            if constexpr (PAIR == 1) {
+                f[e] = sc * (zm.x * w.x - zm.y * w.y);
+                continue;
+            }
+            const cx<T> zc = buf[q * ROW + F::at((N - m) & (N - 1))];
             f[2 * q * N + j] = sc * ((T)0.5 * (zm.x + zc.x) * w.x - (T)0.5 * (zm.y - zc.y) * w.y);
             if (2 * q + 1 < nr)
                 f[(2 * q + 1) * N + j] = sc * ((T)0.5 * (zm.y + zc.y) * w.x - (T)0.5 * (zc.x - zm.x) * w.y);
@@ -331,27 +344,32 @@ __global__ void __launch_bounds__(TINY_THREADS) k_pcg_tiny(TinyArgs<T> A)
             }
         }
         __syncthreads();
-        for (int e = t; e < npair * N; e += TINY_THREADS) {
+        for (int e = t; e < nfft * N; e += TINY_THREADS) {
             const int q = e / N, m1 = e & (N - 1), m2 = (N - m1) & (N - 1);
             const int j1 = dir ? N - 1 - m1 : m1, j2 = dir ? N - 1 - m2 : m2;
-            const bool two = 2 * q + 1 < nr;
-            const T *f0 = f + 2 * q * N, *f1 = two ? f0 + N : f0;
+            const T *f0 = f + PAIR * q * N;
             const T s1 = isc * (m1 == 0 ? sq2 : (T)1), s2 = m1 == 0 ? (T)0 : isc;
             const T a0 = f0[j1] * s1, b0 = f0[j2] * s2;
-            const T a1 = two ? f1[j1] * s1 : (T)0, b1 = two ? f1[j2] * s2 : (T)0;
             const cx<T> w = ptl[m1];
+            if constexpr (PAIR == 1) {
+                buf[q * ROW + F::at(m1)] = {w.x * a0 - w.y * b0, w.x * b0 + w.y * a0};
+                continue;
+            }
+            const bool two = 2 * q + 1 < nr;
+            const T *f1 = two ? f0 + N : f0;
+            const T a1 = two ? f1[j1] * s1 : (T)0, b1 = two ? f1[j2] * s2 : (T)0;
             buf[q * ROW + F::at(m1)] = {(w.x * a0 - w.y * b0) - (w.x * b1 + w.y * a1),
                                         (w.x * b0 + w.y * a0) + (w.x * a1 - w.y * b1)};
         }
         __syncthreads();
-        F::run(buf, twl, npair, t);
+        F::run(buf, twl, nfft, t);
 #pragma unroll
         for (int j = 0; j < TINY_PPT; ++j) {
             const int e = t + TINY_THREADS * j, i = e / N, k = e & (N - 1);
             z[j] = 0.0;
             if (e >= n) continue;
-            const cx<T> v = buf[(i >> 1) * ROW + F::at((k & 1) ? N - 1 - (k >> 1) : k >> 1)];
-            const T s = ((i & 1) ? v.y : v.x) * invN;
+            const cx<T> v = buf[i / PAIR * ROW + F::at((k & 1) ? N - 1 - (k >> 1) : k >> 1)];
+            const T s = (PAIR == 2 && (i & 1) ? v.y : v.x) * invN;
             z[j] = (double)((dir && (k & 1)) ? -s : s);
         }
     };

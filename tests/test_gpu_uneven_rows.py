@@ -45,8 +45,9 @@ def test_apply(ax, orc, nr, nz, bc):
         assert worst_row(host(z), orc.precond(oop, r)) <= 1e-5
 
 
-# one step of PCG from zero is the preconditioned residual times a scalar
-@pytest.mark.parametrize("nr,nz", [(512, 2048)])
+# one step of PCG from zero is the preconditioned residual times a scalar: block-wide
+# rows, and grids whose solve is one workgroup
+@pytest.mark.parametrize("nr,nz", [(512, 2048), (256, 16), (127, 32), (64, 64), (63, 64), (31, 128), (2, 128)])
 @pytest.mark.parametrize("bc", [0, 1])
 def test_first_iterate(ax, orc, nr, nz, bc):
     kappa, q, r, oop = problem(orc, nr, nz, bc, nr % 2)
