@@ -369,9 +369,11 @@ __device__ inline double block_total(const double *__restrict__ parts, int n, do
     return s;
 }
 
-// Has the value computed here: the compiler's code sinking moves LDS reads whose
-// results are first used in a later block down past the workgroup barriers in
-// between, where others already overwrite the buffer.
+// Has the value computed here.  LLVM's machine sinking (ROCm 7.2) moves an LDS read
+// whose result is first used in a later block into that block, past workgroup
+// barriers in between (s_barrier is no memory access to it), where others may
+// already overwrite the buffer.  Needed where a function's LDS reads are used only
+// by its caller, under a condition, and the buffer is used again.
 template <typename T>
 __device__ __forceinline__ void in_register(T &v) { asm volatile("" : "+v"(v)); }
 

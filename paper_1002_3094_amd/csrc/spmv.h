@@ -104,10 +104,11 @@ __host__ __device__ inline int spmv_fold(int nr, int nz, int chunk)
 
 // z comes in the preconditioner's own type ZT: an FP32 preconditioner's z
 // holds float values, so as floats it is the same vector in half the bytes.
-// With the x update here and z so, an FP32 iteration moves 114 bytes a point
-// instead of 130: 541 against 594 us at 4096^2 (SpMV 195 -> 222, forward
-// 207 -> 150, inverse 119 -> 105), 25.5 against 26.9 us for SpMV and forward
-// at 1024^2, 7.5 against 8.5 ms for 24 uneven problems.
+// With the x update here and z so, an FP32 iteration moves 16 bytes a point less,
+// 117 instead of 133 in strips of four rows and 120 instead of 136 in the per-mode
+// form: 541 against 594 us at 4096^2 (SpMV 195 -> 222, forward 207 -> 150, inverse
+// 119 -> 105), 25.5 against 26.9 us for SpMV and forward at 1024^2, 7.5 against
+// 8.5 ms for 24 uneven problems.
 template <typename ZT, bool PR, int RW, int CHUNK, bool FOLD = false>
 __device__ __forceinline__ void spmv_tiles(const ZT *__restrict__ z, const double *__restrict__ pold,
                                            double *__restrict__ pnew, double *__restrict__ q, double *__restrict__ x,

@@ -8,18 +8,20 @@
 // CU: x, r and p in registers (four points a thread), p (for its neighbours),
 // the spectra and the r-solves' pivots in LDS.  Per iteration:
 //   - the SpMV from LDS; three block-wide sums (p.q, ||r||^2, r.z);
-//   - the z-transforms of two rows at a time through one complex radix-8 FFT
-//     (the pairing and scalings of zfwd_body / zinv_body), all pairs at once,
-//     eight values a thread;
+//   - the z-transforms of all rows at once through complex radix-8 FFTs, two rows
+//     each in FP64 and one in FP32 (the pairing and scalings of zfwd_body /
+//     zinv_body), eight values a thread;
 //   - one r-system per z-mode, two threads to a mode: both ends are eliminated
 //     towards the middle row, whose value then runs back to both ends (pivots
 //     formed once per solve, so that a step is one dependent multiply-add).
-// What bounds it is latency inside one CU: some 45k clocks an iteration at
-// 64 x 64 FP64, of which the two FFT passes take 6k, the r-solves' serial chains
-// 9k, and the rest is the barriers between a dozen short phases and the
-// coefficients' way from L2.  A whole solve, as launches and here (us):
-//   64 x 64 FP64 557 -> 342      32 x 128 FP32 570 -> 352
-//   128 x 32 FP64 572 -> 418     250 x 16 FP32 602 -> 466
+// What bounds it is latency inside one CU.  An iteration at 64 x 64 FP64 takes some
+// 30 000 clocks (13.8 us): the r-solves' serial chains 8000, the two FFTs 4800, the
+// passes that bring rows to them and spectra from them 8400, the three block-wide
+// sums 5900 (with the coefficients' way from L2 during the first), the SpMV and p
+// 2800; eighteen workgroup barriers are in these.  At 250 x 16 the r-solves are
+// 24 000 of 46 000.  A whole solve, as launches and here (us):
+//   64 x 64 FP64 531 -> 331, FP32 509 -> 296      32 x 128 FP32 542 -> 309, FP64 566 -> 365
+//   128 x 32 FP64 535 -> 391, FP32 511 -> 354     250 x 16 FP32 534 -> 432, FP64 576 -> 482
 #include "xform.h"
 
 namespace axipcg {
@@ -474,8 +476,8 @@ void tiny_launch(const TinyArgs<T> &a, hipStream_t s)
 // Grids the one-workgroup solve takes: up to 4096 points (four a thread, whose
 // vectors then fit registers and LDS), rows of 16 .. 128 points (shorter ones
 // leave the r-solves to a few threads) and lines of up to 256 rows, what 4096
-// points of such rows hold.  A solve of 4096 points takes 342 .. 466 us here
-// and 557 .. 602 us as launches; above 4096 the launches' work begins to count
+// points of such rows hold.  A solve of 4096 points takes 296 .. 482 us here
+// and 509 .. 576 us as launches; above 4096 the launches' work begins to count
 // and one CU's registers no longer hold the vectors.
 bool tiny_usable(const Operator &op)
 {
