@@ -96,7 +96,7 @@ __global__ void __launch_bounds__(64 * R) k_strip_one(OneArgs<T> A)
             red_lane(A.G, lane, S, lo, m);
             for (int w = threadIdx.x >> 6; w < cnt; w += R) {
                 RedFac<T, LMAX> f;
-                f.load(A.fac, l0 + w, red_rows(A.G), A.ln.cb, lo, m, S, lane);
+                f.template load<false>(A.fac, l0 + w, red_rows(A.G), A.ln.cb, lo, m, S, lane);
                 f.solve(base2 + w * A.G, base2 + (cnt + w) * A.G, A.G, lo, m, S, lane);
             }
             store_red<T, false>(A.red_x, N, A.G, l0, cnt, base2);

@@ -260,27 +260,38 @@ __host__ __device__ inline int red_rows(int G)
 template <typename T, int LMAX>
 struct RedFac {
     T inv[LMAX], c[LMAX], cj[LMAX], a0, al[6], ga[6], piv;
-    // rows [lo, lo + m) of the lane, S lanes with rows; L the layout's rows per
-    // lane (L <= LMAX); cj: the couplings of the interface rows to the next strips
+    // rows [lo, lo + m) of the lane, S lanes with rows (FULL: all 64, so that the
+    // loads' offsets are constants); L the layout's rows per lane (L <= LMAX);
+    // cj: the couplings of the interface rows to the next strips
+    template <bool FULL>
     __device__ __forceinline__ void load(const T *__restrict__ fac, int l, int L, const T *__restrict__ cb, int lo,
                                          int m, int S, int lane)
     {
-        const bool in = lane < S;   // the others: zeros, which solve() turns into zeros
-        const T *f = fac + (size_t)l * red_items(L) * S + lane;
+        const bool in = FULL || lane < S;   // the others read the last lane's and take zeros
+        const int st = FULL ? 64 : S;
+        const T *f = fac + (size_t)l * red_items(L) * st + (in ? lane : st - 1);
 #pragma unroll
         for (int t = 0; t < LMAX; ++t) {
-            inv[t] = in && t < L - 1 ? f[t * S] : (T)0;
-            c[t] = in && t < L ? f[(L - 1 + t) * S] : (T)0;
+            inv[t] = t < L - 1 ? f[t * st] : (T)0;
+            c[t] = t < L ? f[(L - 1 + t) * st] : (T)0;
             cj[t] = t < m ? cb[(lo + t) * 4 + 3] : (T)0;
         }
-        f += (2 * L - 1) * S;
-        a0 = in ? f[0] : (T)0;
+        f += (2 * L - 1) * st;
+        a0 = f[0];
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-            al[k] = in ? f[(1 + k) * S] : (T)0;
-            ga[k] = in ? f[(7 + k) * S] : (T)0;
+            al[k] = f[(1 + k) * st];
+            ga[k] = f[(7 + k) * st];
         }
-        piv = in ? f[13 * S] : (T)0;
+        piv = f[13 * st];
+        if constexpr (!FULL) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                al[k] = in ? al[k] : (T)0;
+                ga[k] = in ? ga[k] : (T)0;
+            }
+            piv = in ? piv : (T)0;
+        }
     }
     // te, tg: E1 and G0 of the mode's strips (LDS); the solution replaces te
     // (every lane has read its values of te before any is written).

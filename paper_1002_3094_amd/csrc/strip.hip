@@ -102,7 +102,7 @@ k_strip_reduced_f(const T *__restrict__ red_e, const T *__restrict__ red_g, T *_
     int S, lo, m;
     red_lane(G, lane, S, lo, m);
     RedFac<T, LMAX> f;
-    f.load(fac, l0 + w, LMAX, cb, lo, m, S, lane);
+    f.template load<(LMAX > 1)>(fac, l0 + w, LMAX, cb, lo, m, S, lane);   // (two rows a lane: more than 64 strips)
     stage_red<T, VEC>(red_e, red_g, N, G, l0, MT, te);
     if (g.mode != 0 && tridiag_gate(st, partials, g, red, blockIdx.x, g.mode == 1 ? &pre : nullptr) != ST_RUN)
         return;
