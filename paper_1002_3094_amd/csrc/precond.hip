@@ -156,18 +156,28 @@ bool twiddles_in_lds(int N) { return 3 * (size_t)N * sizeof(cx<T>) <= 65536; }
 template <typename T>
 size_t transform_lds(int N) { return (twiddles_in_lds<T>(N) ? 3 : 2) * (size_t)N * sizeof(cx<T>); }
 
+// Rows that the radix-8 block-wide kernels (bxform.h) transform: 4096 points, 2048 in
+// FP64 (which would spill in one wave), and up to 640 rows of 2048 in FP32.  More
+// rows than that fill the chip's SIMDs with one wave each, which needs no barriers
+// (outside strips; block-wide and one-wave, us an apply: 256 rows 18.9 and 23.4, 600
+// rows 32.4 and 32.6, 777 rows 39.3 and 36.6, 2048 rows 61.1 and 53.5; a PCG iteration
+// 34.0 and 43.9, 58.3 and 60.5, 71.2 and 68.3, 136.7 and 139.0).
+inline bool block8(int nr, int nz, int prec)
+{
+    return nz >= 4096 || (nz == 2048 && (prec == AXIPCG_PREC_FP64 || nr <= 640));
+}
+
 // Rows per transform workgroup of the block-wide forms: two, which share one
 // complex FFT, when that still leaves at least 256 workgroups, else one.  Sharing
 // puts rounding of the larger row's size into the smaller one: in FP32 that can be
 // all of a row 1e-7 times its partner.  So FP32 rows share only where they are 4096
 // long and even in number; elsewhere it gains little (PCG solves, one row and two:
 // 512 rows of 2048 points 1210 and 1213 us, 513 rows of 4096 2597 and 2393).
-inline bool block8(int nz) { return nz >= 2048; }
 inline int transform_rows(int nr, int nz, int prec)
 {
     if (nr < 512) return 1;
     if (prec == AXIPCG_PREC_FP32) return (nz >= 4096 && nr % 2 == 0) ? 2 : 1;
-    return (block8(nz) || nr % 2 == 0) ? 2 : 1;   // bxform.h pairs any count, xform.h an even one
+    return (block8(nr, nz, prec) || nr % 2 == 0) ? 2 : 1;   // bxform.h pairs any count, xform.h an even one
 }
 
 template <typename T, int BC, int ROWS>
@@ -186,8 +196,7 @@ void zfwd_ttr(const Operator &op, const ZfwdArgs &a, hipStream_t s)
 }
 
 // Rows per workgroup of the one-wave transforms for length N, 0 when N has
-// no one-wave plan (then block-wide kernels run, as they do for unbatched rows of
-// 2048 outside the strips).
+// no one-wave plan (then block-wide kernels run, as they do where block8 says so).
 template <typename T>
 int wave_plan_rows(int N)
 {
@@ -240,10 +249,16 @@ void zfwd_t(const Operator &op, const ZfwdArgs &a, hipStream_t s)
     case 256: return zfwd_wave<T, BC, 2>(op, a, s);
     case 512: return zfwd_wave<T, BC, 4>(op, a, s);
     case 1024: return zfwd_wave<T, BC, 8>(op, a, s);
+    case 2048:
+        if constexpr (sizeof(T) == 4) {
+            if (!block8(op.nr, 2048, AXIPCG_PREC_FP32)) return zfwd_wave<T, BC, 16>(op, a, s);
+        }
+        break;
     default: break;
     }
-    const int rows = transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32);
-    if (block8(op.nz)) {
+    constexpr int prec = sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32;
+    const int rows = transform_rows(op.nr, op.nz, prec);
+    if (block8(op.nr, op.nz, prec)) {
         if (op.nz == 2048) {
             if constexpr (sizeof(T) == 8) {
                 if (rows == 2) return zfwd8_t<T, BC, 2048, 2>(op, a, s);
@@ -356,10 +371,16 @@ void zinv_t(const Operator &op, const ZinvArgs &a, hipStream_t s)
     case 256: return zinv_wave<T, BC, 2>(op, a, s);
     case 512: return zinv_wave<T, BC, 4>(op, a, s);
     case 1024: return zinv_wave<T, BC, 8>(op, a, s);
+    case 2048:
+        if constexpr (sizeof(T) == 4) {
+            if (!block8(op.nr, 2048, AXIPCG_PREC_FP32)) return zinv_wave<T, BC, 16>(op, a, s);
+        }
+        break;
     default: break;
     }
-    const int rows = transform_rows(op.nr, op.nz, sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32);
-    if (block8(op.nz)) {
+    constexpr int prec = sizeof(T) == 8 ? AXIPCG_PREC_FP64 : AXIPCG_PREC_FP32;
+    const int rows = transform_rows(op.nr, op.nz, prec);
+    if (block8(op.nr, op.nz, prec)) {
         if (op.nz == 2048) {
             if constexpr (sizeof(T) == 8) {
                 if (rows == 2) return zinv8_t<T, BC, 2048, 2>(op, a, s);
@@ -449,9 +470,9 @@ static int strip_handle_rows(const Operator &op, int prec)
 // can serve the row count: the strips' one-wave
 // transforms (32 points a lane) then occupy half of the 1024 SIMDs or fewer, one
 // wave each, and the r-solve's lines are short.  PCG solves, strips and block-wide
-// (us): 48 rows 1001 and 686, 256 rows 1186 and 864, 512 rows 1360 and 1205, 777
-// rows 1644 and 1696, 1024 rows 1843 and 1846; Chebyshev solves of 512 rows 1502
-// and 1315, of 777 1880 and 2012.
+// (us): 48 rows 1001 and 686, 256 rows 1186 and 864, 512 rows 1360 and 1207;
+// Chebyshev solves of 512 rows 1502 and 1336.  Above, strips are no slower (777 rows
+// 1644 against 1696 even with two rows to an FFT, Chebyshev 1880 against 2012).
 int strip_solve_rows(const Operator &op, int prec)
 {
     const bool single = op.fused_enabled && op.nr % 4 == 0;
@@ -464,7 +485,7 @@ int transform_blocks(const Operator &op, int prec)
     const int sr = strip_solve_rows(op, prec);
     if (strip_usable(op, prec, sr)) return (op.nr + sr - 1) / sr;
     const int wr = (prec == AXIPCG_PREC_FP32) ? wave_plan_rows<float>(op.nz) : wave_plan_rows<double>(op.nz);
-    if (wr > 0 && !block8(op.nz)) return (op.nr + wr - 1) / wr;
+    if (wr > 0 && !block8(op.nr, op.nz, prec)) return (op.nr + wr - 1) / wr;
     const int rows = transform_rows(op.nr, op.nz, prec);
     return (op.nr + rows - 1) / rows;
 }

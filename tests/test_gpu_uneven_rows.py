@@ -34,7 +34,7 @@ def worst_row(z, ref):
     return (np.linalg.norm(z - ref, axis=1) / np.linalg.norm(ref, axis=1)).max()
 
 
-@pytest.mark.parametrize("nr,nz", [(512, 2048), (515, 2048), (513, 4096)])
+@pytest.mark.parametrize("nr,nz", [(512, 2048), (515, 2048), (700, 2048), (513, 4096)])
 @pytest.mark.parametrize("bc", [0, 1])
 def test_apply(ax, orc, nr, nz, bc):
     kappa, q, r, oop = problem(orc, nr, nz, bc, nr % 2)
