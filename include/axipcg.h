@@ -154,8 +154,9 @@ int axipcg_precond_apply(axipcg_op_t op, const double *r, double *z, int prec, v
  * 4 whatever the height (their in-loop kernels need the registers of 4-wave
  * workgroups).  Unless set_strips was called for the handle (with 1 too), or its
  * single launches are on and nr is a multiple of 4, FP32 solves of at most 512
- * rows of length 2048 run the per-mode r-solve (faster there); standalone applies
- * use the strips.  strips_info reports the solves' strips.
+ * rows of length 2048 run the per-mode r-solve (faster there).  So do, unless
+ * set_strips was called, standalone applies of up to 64 rows that 4 does not divide
+ * and solves of an even number of them.  strips_info reports the solves' strips.
  * strips_info reports whether the strip form is used for `prec` and its
  * strip count (host pointers, may be NULL). */
 int axipcg_op_set_strips(axipcg_op_t op, int enable);

@@ -464,6 +464,15 @@ static int strip_handle_rows(const Operator &op, int prec)
     return (op.strip_rows == 8 && prec == AXIPCG_PREC_FP32 && op.nz == 2048) ? 4 : op.strip_rows;
 }
 
+// Few rows that strips of four do not divide, with the handle's strips not set: the
+// completed last strip is work for nothing and the per-mode r-solve's lines are short.
+// Standalone applies go per mode at up to 64 such rows (FP64 rows of 1024, strips and
+// per mode: 2 rows 18.4 and 15.4 us, 26 rows 19.0 and 17.6, 62 rows 19.3 and 18.4,
+// 97 rows 19.4 and 20.4), solves at even counts up to 64, whose lines fall into two
+// rows a lane without guards (Chebyshev iterations, same rows: 6 rows 26.3 and
+// 24.1 us, 62 rows 27.4 and 26.0; odd counts differ by -5 ... +6 %).
+static bool few_ragged_rows(const Operator &op) { return op.nr % 4 != 0 && op.nr <= 64 && !op.strips_set; }
+
 // The solves leave strips for block-wide transforms and the per-mode r-solve
 // (0 returned) at up to 512 FP32 rows of 2048 points, unless the handle's strips
 // were set or its single launches, which are whole strips of four rows, are on and
@@ -477,6 +486,7 @@ int strip_solve_rows(const Operator &op, int prec)
 {
     const bool single = op.fused_enabled && op.nr % 4 == 0;
     if (prec == AXIPCG_PREC_FP32 && op.nz == 2048 && op.nr <= 512 && !op.strips_set && !single) return 0;
+    if (few_ragged_rows(op) && op.nr % 2 == 0) return 0;
     return strip_handle_rows(op, prec);
 }
 
@@ -640,9 +650,9 @@ void launch_b_tridiag(const ProbDesc *d, int n, int blocks, int prec, const TriG
     AXI_CHECK_HIP(hipGetLastError());
 }
 
-void launch_zfwd(const Operator &op, int prec, const ZfwdArgs &a, hipStream_t s)
+// The per-mode form's three launches.
+static void mode_zfwd(const Operator &op, int prec, const ZfwdArgs &a, hipStream_t s)
 {
-    if (strip_usable(op, prec, strip_solve_rows(op, prec))) return strip_fwd(op, prec, strip_solve_rows(op, prec), a, s);
     if (prec == AXIPCG_PREC_FP32) {
         if (op.bc_z == DIR) zfwd_t<float, DIR>(op, a, s);
         else zfwd_t<float, AXIPCG_Z_NEUMANN>(op, a, s);
@@ -652,9 +662,8 @@ void launch_zfwd(const Operator &op, int prec, const ZfwdArgs &a, hipStream_t s)
     }
 }
 
-void launch_zinv(const Operator &op, int prec, const ZinvArgs &a, hipStream_t s)
+static void mode_zinv(const Operator &op, int prec, const ZinvArgs &a, hipStream_t s)
 {
-    if (strip_usable(op, prec, strip_solve_rows(op, prec))) return strip_inv(op, prec, strip_solve_rows(op, prec), a, s);
     if (prec == AXIPCG_PREC_FP32) {
         if (op.bc_z == DIR) zinv_t<float, DIR>(op, a, s);
         else zinv_t<float, AXIPCG_Z_NEUMANN>(op, a, s);
@@ -664,12 +673,29 @@ void launch_zinv(const Operator &op, int prec, const ZinvArgs &a, hipStream_t s)
     }
 }
 
+static void mode_tridiag(const Operator &op, int prec, const TriGate &g, hipStream_t s)
+{
+    if (prec == AXIPCG_PREC_FP32) tridiag_t<float>(op, g, s);
+    else tridiag_t<double>(op, g, s);
+}
+
+void launch_zfwd(const Operator &op, int prec, const ZfwdArgs &a, hipStream_t s)
+{
+    if (strip_usable(op, prec, strip_solve_rows(op, prec))) return strip_fwd(op, prec, strip_solve_rows(op, prec), a, s);
+    mode_zfwd(op, prec, a, s);
+}
+
+void launch_zinv(const Operator &op, int prec, const ZinvArgs &a, hipStream_t s)
+{
+    if (strip_usable(op, prec, strip_solve_rows(op, prec))) return strip_inv(op, prec, strip_solve_rows(op, prec), a, s);
+    mode_zinv(op, prec, a, s);
+}
+
 void launch_tridiag(const Operator &op, int prec, const TriGate &g, hipStream_t s)
 {
     if (strip_usable(op, prec, strip_solve_rows(op, prec)))
         return strip_reduced(op, prec, strip_solve_rows(op, prec), g, s);
-    if (prec == AXIPCG_PREC_FP32) tridiag_t<float>(op, g, s);
-    else tridiag_t<double>(op, g, s);
+    mode_tridiag(op, prec, g, s);
 }
 
 // Standalone applies of FP32 rows of length 2048 use strips of 8 rows when
@@ -677,7 +703,7 @@ void launch_tridiag(const Operator &op, int prec, const TriGate &g, hipStream_t 
 // workgroups without the PCG vectors, and the reduced system halves).
 void precond_apply_impl(const Operator &op, const double *r, double *z, int prec, hipStream_t s)
 {
-    int rows = strip_handle_rows(op, prec);
+    int rows = few_ragged_rows(op) ? 0 : strip_handle_rows(op, prec);
     if (rows == 4 && prec == AXIPCG_PREC_FP32 && op.nz == 2048 && op.nr % 8 == 0 && strip_usable(op, prec, 8)) rows = 8;
     if (rows > 0 && strip_usable(op, prec, rows)) {
         ZfwdArgs fa;
@@ -691,11 +717,11 @@ void precond_apply_impl(const Operator &op, const double *r, double *z, int prec
     }
     ZfwdArgs fa;
     fa.rin = r;
-    launch_zfwd(op, prec, fa, s);
-    launch_tridiag(op, prec, TriGate{}, s);
+    mode_zfwd(op, prec, fa, s);
+    mode_tridiag(op, prec, TriGate{}, s);
     ZinvArgs ia;
     ia.zout = z;
-    launch_zinv(op, prec, ia, s);
+    mode_zinv(op, prec, ia, s);
 }
 
 }  // namespace axipcg
