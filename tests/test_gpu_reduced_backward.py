@@ -12,15 +12,6 @@ from tests.gpu_util import dev, host, spectral_norm_estimate
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(scope="module")
-def ax():
-    import torch
-    assert torch.cuda.is_available()
-    from paper_1002_3094_amd import axipcg
-    axipcg.lib()
-    return axipcg
-
-
 @pytest.mark.parametrize("strips", [1, 2, 63, 64, 65, 128, 129, 256, 257, 512, 513, 1024])
 @pytest.mark.parametrize("prec", [0, 1])
 def test_backward_error(ax, orc, strips, prec):

@@ -15,15 +15,6 @@ from tests.gpu_util import dev, host, rel
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(scope="module")
-def ax():
-    import torch
-    assert torch.cuda.is_available()
-    from paper_1002_3094_amd import axipcg
-    axipcg.lib()
-    return axipcg
-
-
 @pytest.mark.parametrize("nr,nz", [(1024, 32), (1025, 16), (1537, 128), (1539, 64), (2561, 32), (2050, 8), (3077, 2)])
 @pytest.mark.parametrize("polak", [False, True])
 def test_iterate(ax, orc, nr, nz, polak):

@@ -14,15 +14,6 @@ from tests.gpu_util import dev, host
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(scope="module")
-def ax():
-    import torch
-    assert torch.cuda.is_available()
-    from paper_1002_3094_amd import axipcg
-    axipcg.lib()
-    return axipcg
-
-
 def problem(orc, nr, nz, bc, first):
     kappa, q = np.full((nr, nz), 1.5), np.full((nr, nz), 1.0)
     r = np.random.default_rng(nr + nz).standard_normal((nr, nz))

@@ -18,15 +18,6 @@ from tests.gpu_util import dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(scope="module")
-def ax():
-    import torch
-    assert torch.cuda.is_available()
-    from paper_1002_3094_amd import axipcg
-    axipcg.lib()
-    return axipcg
-
-
 def taps_of(flat):
     """Per layer the nine taps' weight gradients, [9][cin cout]."""
     return [flat[o:o + 9 * ci * co].reshape(9, -1) for o, ci, co in zip(onn.OFFSETS, onn.CIN, onn.COUT)]
