@@ -39,6 +39,15 @@ struct LagCoefs {
     }
 };
 
+// Harmonics stepped in round c of n: LC, in the last round what is left, up to
+// the next multiple of 16 (the unrolled steps).  (All LC of them: 674 us instead
+// of 269 for the synthesis of 4096 traces of 20001 samples from one harmonic.)
+__device__ inline int lag_steps(int n, int c)
+{
+    const int left = n - c * LC;
+    return left < LC ? (left + 15) & ~15 : LC;
+}
+
 __device__ inline double lag_start(double x, double eta, int alpha)
 {
     double r0 = 1.0;   // rt_0 = 1/sqrt(alpha!)
@@ -86,24 +95,25 @@ k_laguerre_coeffs(const double *__restrict__ f, int nt, double dt, double eta, i
             if (steps) {
                 if (c == rounds) continue;
                 const LagCoefs &l = lc[c & 1];
-#pragma unroll 16
-                for (int t = 0; t < LC; ++t) {
-                    prod[c & 1][t][lane] = w * cur;
-                    const double nx = l.next(t, x, prev, cur);
-                    prev = cur;
-                    cur = nx;
-                }
+                for (int t0 = 0, nt_c = lag_steps(n, c); t0 < nt_c; t0 += 16)
+#pragma unroll
+                    for (int t = t0; t < t0 + 16; ++t) {
+                        prod[c & 1][t][lane] = w * cur;
+                        const double nx = l.next(t, x, prev, cur);
+                        prev = cur;
+                        cur = nx;
+                    }
             } else {
                 if (c + 1 < rounds) lc[(c + 1) & 1].fill((c + 1) * LC, lane, alpha);
                 const int m = (c - 1) * LC + lane;
-                if (c == 0) continue;
+                if (c == 0 || m >= n) continue;   // rows past n are not written
                 double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
                 for (int i = 0; i < 64; i += 4)
 #pragma unroll
                     for (int u = 0; u < 4; ++u) s[u] += prod[(c - 1) & 1][lane][i + u];
                 const double t = (s[0] + s[1]) + (s[2] + s[3]);
-                if (m < n) out[m] = (gr == (int)blockIdx.x) ? t : out[m] + t;
+                out[m] = (gr == (int)blockIdx.x) ? t : out[m] + t;
             }
         }
         __syncthreads();
@@ -201,14 +211,15 @@ k_laguerre_synth(const double *__restrict__ Q, int n, int nrec, int nt, double d
     for (int c = 0; c < rounds; ++c) {
         __syncthreads();
         const LagCoefs &l = lc[c & 1];
-#pragma unroll 16
-        for (int t = 0; t < LC; ++t) {
+        for (int t0 = 0, nt_c = lag_steps(n, c); t0 < nt_c; t0 += 16)
 #pragma unroll
-            for (int q = 0; q < RB; ++q) acc[q] += qs[c & 1][t][q] * cur;
-            const double nx = l.next(t, x, prev, cur);
-            prev = cur;
-            cur = nx;
-        }
+            for (int t = t0; t < t0 + 16; ++t) {
+#pragma unroll
+                for (int q = 0; q < RB; ++q) acc[q] += qs[c & 1][t][q] * cur;
+                const double nx = l.next(t, x, prev, cur);
+                prev = cur;
+                cur = nx;
+            }
     }
     if (j >= nt) return;
 #pragma unroll
