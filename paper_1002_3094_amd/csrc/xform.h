@@ -20,16 +20,16 @@ template <typename T>
 __device__ inline const typename vec2_of<T>::type *stage_twiddles(const typename vec2_of<T>::type *tw,
                                                                   typename vec2_of<T>::type *lds, int N)
 {
-    // eight loads in flight per round (N <= 2048, >= 64 threads: at most four rounds)
-    for (int base = 0; base < N; base += 8 * (int)blockDim.x) {
-        typename vec2_of<T>::type v[8];
+    // rows of up to 128 points and 64 threads or more: a round of two loads
+    for (int base = 0; base < N; base += 2 * (int)blockDim.x) {
+        typename vec2_of<T>::type v[2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < 2; ++j) {
             const int k = base + (int)threadIdx.x + j * (int)blockDim.x;
             v[j] = tw[k < N ? k : 0];
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < 2; ++j) {
             const int k = base + (int)threadIdx.x + j * (int)blockDim.x;
             if (k < N) lds[k] = v[j];
         }
