@@ -204,13 +204,12 @@ __device__ __forceinline__ void zinv_body(const T *__restrict__ spec, ZOut<T, MO
     constexpr bool CHEB = (MODE == 3 || MODE == 4);
     using V2 = typename vec2_of<T>::type;
     const int i0 = xcd_swizzle(vb, nr / ROWS) * ROWS;
-    // read with the row and the twiddles and acted on after them (every
-    // workgroup alike), so that one trip to memory serves all
-    const int done = MODE != 0 ? st->done : 0;
-    auto stopped = [&]() {
-        if (done && MODE == 1) x_finish(fin, st, (size_t)i0 * N, ROWS * N, threadIdx.x, blockDim.x);
-        return done != 0;
-    };
+    // acted on before the row is read: the launches that a stopped solve or a
+    // batch's stopped members still make then touch the flag alone
+    if (MODE != 0 && st->done) {
+        if (MODE == 1) x_finish(fin, st, (size_t)i0 * N, ROWS * N, threadIdx.x, blockDim.x);
+        return;
+    }
     extern __shared__ char smem_raw[];
     cx<T> *a = reinterpret_cast<cx<T> *>(smem_raw);
     cx<T> *b = a + N;
@@ -302,7 +301,6 @@ __device__ __forceinline__ void zinv_body(const T *__restrict__ spec, ZOut<T, MO
             load_r(0);
             load_r(1);
         }
-        if (stopped()) return;
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < KPT; ++j) {
@@ -332,7 +330,6 @@ __device__ __forceinline__ void zinv_body(const T *__restrict__ spec, ZOut<T, MO
             }
         }
         if (PCGM) load_r(0);
-        if (stopped()) return;
         __syncthreads();
         const cx<T> *res = fft_stockham<T>(a, b, N, twp);
         store(res, 0, 0);
